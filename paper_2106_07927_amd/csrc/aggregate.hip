@@ -94,14 +94,65 @@ int merge_mode(int npaths, int p2) { return (slices_u8(p2) ? 2 : 0) + (npaths ==
 
 }  // namespace
 
+// Lane layouts per disparity range, all with identical results; the variants
+// trade waves and the length of a line's chain against total work.
+int path_variants(int ndisp) {
+    if (ndisp <= 32) return 1;
+    if (ndisp <= 64) return 2;
+    if (ndisp <= 128) return 3;
+    return 2;
+}
+
+namespace {
+// index into kPathLayouts
+int path_layout_id(int ndisp, int variant) {
+    if (ndisp <= 2) return 0;
+    if (ndisp <= 4) return 1;
+    if (ndisp <= 8) return 2;
+    if (ndisp <= 16) return 3;
+    if (ndisp <= 32) return 4;
+    if (ndisp <= 64) return 5 + (variant == 1);
+    if (ndisp <= 128) return 7 + (variant == 1 || variant == 2 ? variant : 0);
+    return 10 + (variant == 1);
+}
+}  // namespace
+
+PathLayout path_layout(int ndisp, int variant) { return kPathLayouts[path_layout_id(ndisp, variant)]; }
+
+// Variant used when none is asked for (variant < 0), from timed sweeps of
+// 160x120 .. 1920x1080 with 4 and 8 paths (microseconds per frame below).
+int default_variant(int width, int height, int ndisp, int npaths) {
+    if (ndisp <= 32) return 0;
+    const int b0 = path_blocks(width, height, ndisp, npaths, 0);
+    if (ndisp <= 64) {
+        // helpers pay while every block has a compute unit of its own:
+        // 640x480, 4 paths (200 blocks) 94 against 104; 480x360, 8 paths
+        // (270 blocks) 101 against 93; 1920x1080 515 against 465
+        return b0 <= 256 ? 0 : 1;
+    }
+    if (ndisp <= 128) {
+        // up to two blocks per compute unit the shortest chains win (640x512:
+        // 173 against 201 and 181); beyond that whole lines per wave do
+        // (1920x1080: 934 and 998 against 820), but not where the rows are
+        // the long chains (1242x375: 237, 218, 278; 1920x400: 355, 409, 397)
+        if (b0 <= 512) return 0;
+        if (width > 2 * height) return b0 <= 768 ? 1 : 0;
+        return 2;
+    }
+    // 640x512 272 against 286, 1920x1080 1807 against 1740 (8 paths);
+    // 640x480 223 against 186, 1242x375 276 against 297 (4 paths)
+    const long px = (long)width * height;
+    if (npaths == 4) return px >= 300000 && width <= 2 * height ? 1 : 0;
+    return px >= 400000 ? 1 : 0;
+}
+
 // Launch of the path pass for the layout `l`: the layout's kernels live in
 // their own object (paths.hip, compiled per layout).
 hipError_t launch_paths_any(const Frame* one, const WorkList* wl, int ndisp, int variant, bool u8,
                             int nblocks, hipStream_t stream) {
-    const PathLayout l = path_layout(ndisp, variant);
+    const int id = path_layout_id(ndisp, variant);
 #define SGM_CASE(K)                                                                                  \
-    if (l.nreg_h == kPathLayouts[K].nreg_h && l.lpl_h == kPathLayouts[K].lpl_h &&                   \
-        l.nreg_o == kPathLayouts[K].nreg_o && l.lpl_o == kPathLayouts[K].lpl_o)                     \
+    if (id == K)                                                                                     \
         return one ? launch_paths_layout_id<K>(*one, ndisp, u8, nblocks, stream)                     \
                    : launch_paths_batch_layout_id<K>(*wl, ndisp, u8, nblocks, stream);
     SGM_CASE(0)
@@ -120,52 +171,15 @@ hipError_t launch_paths_any(const Frame* one, const WorkList* wl, int ndisp, int
     return hipErrorInvalidValue;
 }
 
-// Lane layouts per disparity range.  Variant 0 is the default; the others
-// trade the horizontal chains' per-step latency (more lanes per line) against
-// total VALU work (more disparities per lane).  All give identical results.
-int path_variants(int ndisp) {
-    if (ndisp <= 32) return 1;
-    if (ndisp <= 64) return 2;
-    if (ndisp <= 128) return 3;
-    return 2;
-}
-
-PathLayout path_layout(int ndisp, int variant) {
-    if (ndisp <= 2) return {1, 1, 1, 1};
-    if (ndisp <= 4) return {1, 2, 2, 1};
-    if (ndisp <= 8) return {1, 4, 4, 1};
-    if (ndisp <= 16) return {1, 8, 4, 2};
-    if (ndisp <= 32) return {1, 16, 4, 4};
-    if (ndisp <= 64) return variant == 1 ? PathLayout{2, 16, 4, 8} : PathLayout{1, 32, 4, 8};
-    if (ndisp <= 128) {
-        if (variant == 1) return {2, 32, 4, 16};
-        if (variant == 2) return {1, 64, 8, 8};
-        return {1, 64, 4, 16};
-    }
-    return variant == 1 ? PathLayout{4, 32, 8, 16} : PathLayout{2, 64, 8, 16};
-}
-
-// Variant used when none is asked for (variant < 0): the layout the tuner
-// measured fastest for frames of this size class.  Large frames have enough
-// horizontal lines to trade per-step latency for fewer instructions.
-int default_variant(int width, int height, int ndisp) {
-    const long px = (long)width * height;
-    if (ndisp <= 32) return 0;
-    if (ndisp > 128) return px >= 400000 ? 1 : 0;    // 1242x375, 1920x1080 at D = 256
-    if (px >= 1500000) return 1;
-    if (ndisp > 64 && px >= 400000) return 2;
-    return 0;
-}
-
 int path_horizontal_blocks(int width, int height, int ndisp, int variant) {
     const PathLayout l = path_layout(ndisp, variant);
-    return pair_blocks(0, width, height, l.lpl_h, l.lpl_o);
+    return pair_blocks(0, width, height, l);
 }
 
 int path_blocks(int width, int height, int ndisp, int npaths, int variant) {
     const PathLayout l = path_layout(ndisp, variant);
     int nb = 0;
-    for (int q = 0; q < npaths / 2; ++q) nb += pair_blocks(q, width, height, l.lpl_h, l.lpl_o);
+    for (int q = 0; q < npaths / 2; ++q) nb += pair_blocks(q, width, height, l);
     return nb;
 }
 
@@ -182,7 +196,7 @@ size_t aggregate_work_bytes(int width, int height, int ndisp, int npaths, int p2
 hipError_t launch_paths(const Frame& f, hipStream_t stream) {
     const int variant = (f.variant >= 0 && f.variant < path_variants(f.ndisp))
                             ? f.variant
-                            : default_variant(f.width, f.height, f.ndisp);
+                            : default_variant(f.width, f.height, f.ndisp, f.npaths);
     const int nb = path_blocks(f.width, f.height, f.ndisp, f.npaths, variant);
     return launch_paths_any(&f, nullptr, f.ndisp, variant, slices_u8(f.p2), nb, stream);
 }

@@ -15,115 +15,160 @@
 // Both directions of a pair cover the same lines, in opposite orders (for a
 // diagonal, the same wrapped pixel sequence backwards).
 //
-// Pairs.  A block holds a forward wave that walks r along a group of lines
-// and a reverse wave that walks -r along the same lines (two such pairs per
-// block).  Each writes its
-// penalty part A (or L, see below) for its own first half of every line
-// into the pair's slice; after a workgroup barrier each adds the value the
-// other wave left at the pixels of its second half and writes the sum.  So a
-// pair slice holds, exactly, A_r + A_-r at every pixel: with P2 <= 127 both
-// lie in [0, P2] and the sum fits a byte; otherwise the slice is uint16 and
-// holds L_r + L_-r.  The selection then reads R/2 slices, not R.  Both waves
-// run the same number of steps T = n + delta (a multiple of the chunk length
-// K): the forward wave's extra steps come after its line's end, the reverse
-// wave's before its start, so that each wave's barrier falls on a chunk
-// boundary of its own.  Extra steps load whatever their offset holds (the
-// loads are range-checked buffer loads), never store, and the reverse wave
-// restarts its recursion after them.
+// Pairs.  A forward wave walks r along a group of lines and a reverse wave
+// walks -r along the same lines; both belong to one block.  The pass writes
+// one slice per pair: with P2 <= 127 the penalty parts A = L - C of both
+// directions lie in [0, P2] and their sum fits a byte; otherwise the slice is
+// uint16 and holds L_r + L_-r.  Either is exact.  The two directions visit a
+// pixel at different times, so one of the two values has to be kept until the
+// other one is there:
+//   first half   each wave walks the first half of its lines and stores only
+//                the first step of every chunk of K steps (a checkpoint, in
+//                the place of the slice that its pixel has anyway);
+//   barrier      of the block;
+//   second half  each wave goes on along the half its partner came from.  For
+//                every chunk it reads the partner's checkpoint, walks the
+//                partner's steps of that chunk again from the cost bytes it
+//                needs itself, and stores the sum of both.
+// So a slice is written once (plus 2 / K of it as checkpoints) and the cost
+// volume is read once per direction.  The pass is bound by that traffic on
+// all but small frames (per volume element 8 + 4 + 1 bytes for 8 paths, where
+// storing the first half's values instead took 8 + 8 + 4); the steps walked
+// twice cost less than the bytes they save: 1920x1080, D = 256: 1910 -> 1114
+// us, 1242x375, D = 128: 182 -> 135 us, with P2 = 880: 320 -> 207 us.
+// In small frames a line is a chain that nothing else hides.  There two more
+// waves per line group (PathLayout::help_*) walk the partner's steps and hand
+// them over through LDS, a chunk ahead: 320x240, D = 64, 4 paths: 30 -> 24 us.
+// Where lines are many the same waves do better on lines of their own.
+//
+// Both waves run the same number of steps T = n + delta (a multiple of K):
+// the forward wave's extra steps come after its line's end, the reverse
+// wave's before its start, so chunks of both cover the same pixels.  Extra
+// steps read zeros (which leave a fresh state as it is) and never store.
 //
 // Lanes.  A line is owned by LPL consecutive lanes; each lane keeps 2*NREG
-// disparities of the path vector as packed uint16 pairs.  The state is the
-// previous pixel's path vector L' (each value C + A <= 255 + P2), and one
-// step reads
-//     L(d) = C(d) + min(X(d), m' + P2) - m',
-//     X(d) = min(L'(d), min(L'(d-1), L'(d+1)) + P1),  m' = min_d L'(d);
-// min(L'(d-1), L'(d+1)) comes from Q_k = min(L'_k, L'_k+1) and one alignbit
-// per register, with one DPP lane shift each way per step; m' is a
-// v_pk_min_u16 tree plus a DPP / permlane all-reduce over the line's lanes,
-// which runs beside X instead of ahead of it.  Disparities beyond D (padding)
-// hold 0x7FFF: never a minimum, and as a neighbour never below m' + P2.
+// consecutive disparities as packed uint16 pairs, register k holding
+// (d0 + k, d0 + NREG + k): the neighbours d +- 1 of a register are then the
+// registers beside it, and only the first and the last one need the lanes
+// beside (one DPP lane shift and one alignbit each way per step).  The state
+// is the path vector up to an offset common to the line, taken off once per
+// chunk; with m its minimum, one step is
+//     V(d) = min(L(d), min(L(d-1), L(d+1)) + P1, m + P2),
+//     A(d) = V(d) - m,  L'(d) = V(d) + C(d).
+// Per register: a minimum, an add, a three-way minimum (v_pk_minimum3_f16 on
+// the integers' bit patterns), a byte permute and an add.  m is a tree over
+// the registers and an all-reduce over the line's lanes that runs beside the
+// neighbour terms.  Disparities beyond D (padding) are lifted by 255 + P2 in
+// every step: as neighbours they never come below m + P2, and m never is one.
 //
-// Memory.  On this GPU family one counter tracks both loads and stores, so a
-// loop that prefetches while it stores would wait for every store each step.
-// The loop therefore runs in chunks of K steps: at a chunk boundary it waits
-// once, issues the loads of the next chunk (cost bytes, and in the second
-// half the partner's values), and computes the K steps from registers.
-// Cost and partner loads and the slice stores go through raw buffer
-// resources: offsets past the volume read as zero and stores there are
-// dropped, so positions beyond a line need no clamping; a lane or step that
-// must not write carries kNoWrite added to its offset.
+// Memory.  Loads run a chunk ahead.  Cost and checkpoint loads and the slice
+// stores go through raw buffer resources: offsets past the volume read as
+// zero and stores there are dropped, so positions beyond a line need no
+// clamping; a lane or step that must not write carries kNoWrite in its offset.
 #include "sgm_internal.h"
 
 #include <type_traits>
 
+#ifndef SGM_PATH_LAYOUT
+#error "paths.hip is compiled once per lane layout: -DSGM_PATH_LAYOUT=<index>"
+#endif
+#if !defined(SGM_PATH_PART) || (SGM_PATH_PART != 0 && SGM_PATH_PART != 1)
+#error "paths.hip is compiled in two parts: -DSGM_PATH_PART=0 (single frame) or 1 (work list)"
+#endif
+
 namespace sgm {
 namespace {
 
-constexpr uint32_t kBig = 0x7FFFu;
-constexpr uint32_t kBig2 = 0x7FFF7FFFu;
-// A block is four waves: the forward waves of two line groups, then their
-// reverse waves.  Four-wave blocks put one wave on each SIMD of a compute
-// unit; two-wave blocks let the dispatcher stack waves of the long
-// horizontal lines on the same SIMD (measured: 227 -> 197 us per frame at
-// 1242x375, D = 128).
+// A block is four waves: one per SIMD of a compute unit (two-wave blocks let
+// the dispatcher stack waves of the long horizontal lines on the same SIMD).
 constexpr int kThreads = 256;
 
 enum Kind : int { kHorizontal = 0, kVertical = 1, kDiagonal = 2 };
 
-// Steps per chunk of the path loop, by lane layout (horizontal lines with one
-// / more packed registers per lane, other lines with <= 4 / 8 registers).
-constexpr int kStepsH1 = 32, kStepsH2 = 16;
-constexpr int kStepsO4 = 16, kStepsO8 = 8;
+// Steps per chunk of the path loop.  Half as many for the vertical and
+// diagonal lines: with 16 their kernels pass 256 registers and only one wave
+// fits a SIMD (1242x375, D = 128, 8 registers per lane: 239 us against 148).
+constexpr int kStepsH = 16, kStepsO = 8;
+
+// Cache policy of the slice stores: 2 = nontemporal.
+constexpr int kStorePolicy = kPathLayouts[SGM_PATH_LAYOUT].stream ? 2 : 0;
+
+// ---- packed pairs ----------------------------------------------------------
+// Minimum of three per half.  NARROW: every half is below 0x7C00, where the
+// bit patterns of non-negative half floats order like the integers
+// (denormals are kept), so one v_pk_minimum3_f16 takes it.
+template <bool NARROW>
+__device__ __forceinline__ uint32_t pk_min3(uint32_t a, uint32_t b, uint32_t c) {
+    if constexpr (NARROW) {
+        typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+        const f16x2 x = __builtin_bit_cast(f16x2, a), y = __builtin_bit_cast(f16x2, b),
+                    z = __builtin_bit_cast(f16x2, c);
+        return __builtin_bit_cast(uint32_t,
+                                  __builtin_elementwise_minimum(__builtin_elementwise_minimum(x, y), z));
+    } else {
+        return pk_min(pk_min(a, b), c);
+    }
+}
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp0(uint32_t v) {      // lanes without a source read 0
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
 
 // ---- cross-lane helpers for lines of up to 64 lanes -----------------------
-template <int GROUP>
-__device__ __forceinline__ uint32_t line_min(uint32_t v) {
-    if constexpr (GROUP <= 16) {
-        return group_min<GROUP>(v);
-    } else {
-        v = group_min<16>(v);
-        // rows (0,1) and (2,3) exchange, then the two halves of the wave
+// Minimum of the packed state over a line, as the same value in both halves
+// of every lane of the line (LPL == 64: of a scalar register).
+template <int NREG, int LPL, bool NARROW>
+__device__ __forceinline__ uint32_t line_min2(const uint32_t (&L)[NREG]) {
+    uint32_t v = L[0];
+    if constexpr (NREG >= 8) {
+        uint32_t w = pk_min3<NARROW>(L[1], L[2], L[3]);
+        v = pk_min3<NARROW>(v, L[4], L[5]);
+        if constexpr (NREG == 16) {
+            w = pk_min3<NARROW>(w, L[8], L[9]);
+            v = pk_min3<NARROW>(v, L[10], L[11]);
+            w = pk_min3<NARROW>(w, L[12], L[13]);
+            v = pk_min3<NARROW>(v, L[14], L[15]);
+        }
+        w = pk_min3<NARROW>(w, L[6], L[7]);
+        v = pk_min(v, w);
+    } else if constexpr (NREG == 4) {
+        v = pk_min3<NARROW>(v, L[1], pk_min(L[2], L[3]));
+    } else if constexpr (NREG == 2) {
+        v = pk_min(v, L[1]);
+    }
+    v = pk_min(v, __builtin_amdgcn_alignbit(v, v, 16));
+    if constexpr (LPL >= 2) v = min(v, dpp0<kDppQuadSwap1>(v));
+    if constexpr (LPL >= 4) v = min(v, dpp0<kDppQuadSwap2>(v));
+    if constexpr (LPL >= 8) v = min(v, dpp0<kDppRowHalfMirror>(v));
+    if constexpr (LPL >= 16) v = min(v, dpp0<kDppRowMirror>(v));
+    if constexpr (LPL == 32) {
         auto s16 = __builtin_amdgcn_permlane16_swap(v, v, false, false);
         v = min((uint32_t)s16[0], (uint32_t)s16[1]);
-        if constexpr (GROUP == 64) {
-            auto s32 = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-            v = min((uint32_t)s32[0], (uint32_t)s32[1]);
-        }
-        return v;
     }
+    if constexpr (LPL == 64) {
+        // row_bcast:15 / row_bcast:31 carry the minimum to lane 63; from there
+        // it travels as a scalar, off the vector chain of the step
+        v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)0xFFFFFFFF, (int)v, 0x142, 0xA, 0xF, false));
+        v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)0xFFFFFFFF, (int)v, 0x143, 0xC, 0xF, false));
+        v = (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+    }
+    return v;
 }
 
-// Minimum over all 64 lanes as a wave-uniform value: row reductions, the
-// row_bcast:15 / row_bcast:31 steps that carry it to lane 63, one readlane.
-// The result lives in a scalar register, so the splat and the cap that
-// follow run on the scalar unit, off the vector chain of the step.
-__device__ __forceinline__ uint32_t wave_min_uniform(uint32_t v) {
-    v = group_min<16>(v);
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)0xFFFFFFFF, (int)v, 0x142, 0xA, 0xF, false));
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)0xFFFFFFFF, (int)v, 0x143, 0xC, 0xF, false));
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+// Value of the next / previous lane (rows of 16 up to LPL == 16, else the
+// whole wave); the caller overrides what crosses a line's edge.
+template <int LPL>
+__device__ __forceinline__ uint32_t lane_next(uint32_t v) {
+    if constexpr (LPL == 1) return 0;
+    else if constexpr (LPL <= 16) return dpp0<kDppRowShl1>(v);
+    else return dpp0<0x130>(v);
 }
-
-template <int GROUP>
-__device__ __forceinline__ uint32_t line_next(uint32_t v, uint32_t edge, bool last) {
-    if constexpr (GROUP <= 16) {
-        return group_next<GROUP>(v, edge, last);
-    } else {
-        const uint32_t r = (uint32_t)__builtin_amdgcn_update_dpp((int)edge, (int)v, 0x130, 0xF, 0xF, false);
-        if constexpr (GROUP == 64) return r;        // wave_shl:1, lane 63 keeps `edge`
-        else return last ? edge : r;
-    }
-}
-
-template <int GROUP>
-__device__ __forceinline__ uint32_t line_prev(uint32_t v, uint32_t edge, bool first) {
-    if constexpr (GROUP <= 16) {
-        return group_prev<GROUP>(v, edge, first);
-    } else {
-        const uint32_t r = (uint32_t)__builtin_amdgcn_update_dpp((int)edge, (int)v, 0x138, 0xF, 0xF, false);
-        if constexpr (GROUP == 64) return r;        // wave_shr:1, lane 0 keeps `edge`
-        else return first ? edge : r;
-    }
+template <int LPL>
+__device__ __forceinline__ uint32_t lane_prev(uint32_t v) {
+    if constexpr (LPL == 1) return 0;
+    else if constexpr (LPL <= 16) return dpp0<kDppRowShr1>(v);
+    else return dpp0<0x138>(v);
 }
 
 // ---- bytes of one lane for one pixel: 2*NREG bytes --------------------------
@@ -208,160 +253,189 @@ __device__ __forceinline__ WideVec<NREG> load_wide(__amdgpu_buffer_rsrc_t rs, ui
     return v;
 }
 
-// bytes 2k, 2k+1 of the vector, zero-extended into a packed pair
+// State registers hold the lane's disparities split in halves: register k is
+// the pair (d0 + k, d0 + NREG + k), so that the neighbours d +- 1 of a whole
+// register are the registers beside it and only the first and the last one
+// need a shift.  These convert from and to memory order.
+
+// register k of 2*NREG bytes in memory order, zero-extended
 template <int NREG>
-__device__ __forceinline__ uint32_t cost_pair(const ByteVec<NREG>& c, int k) {
-    return __builtin_amdgcn_perm(0u, c.w[k >> 1], (k & 1) ? 0x0c030c02u : 0x0c010c00u);
+__device__ __forceinline__ uint32_t byte_pair(const ByteVec<NREG>& c, int k) {
+    if constexpr (NREG == 1) return __builtin_amdgcn_perm(0u, c.w[0], 0x0c010c00u);
+    const int lo = k, hi = NREG + k;                     // byte indices
+    return __builtin_amdgcn_perm(c.w[hi >> 2], c.w[lo >> 2],
+                                 0x0c000c00u | (uint32_t)(lo & 3) | ((uint32_t)(4 + (hi & 3)) << 16));
 }
 
-// Partner values a wave adds before storing: bytes (uint8 slices) or packed
-// uint16 pairs (wide slices); zero in a wave's first half.
-template <int NREG, bool U8>
-struct Partner;
+// Bytes of a lane in state order: word j = bytes (d0 + 2j, d0 + 2j + 1,
+// d0 + NREG + 2j, d0 + NREG + 2j + 1); NREG == 1: the one pair itself, two
+// 16-bit halves.
 template <int NREG>
-struct Partner<NREG, true> {
-    ByteVec<NREG> v;
-    __device__ __forceinline__ void clear() {
-#pragma unroll
-        for (int i = 0; i < ByteVec<NREG>::kWords; ++i) v.w[i] = 0;
-    }
-    template <bool ALIGNED>
-    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, uint32_t elem) {
-        v = load_bytes<NREG, ALIGNED>(rs, elem);
-    }
-};
-template <int NREG>
-struct Partner<NREG, false> {
-    WideVec<NREG> v;
-    __device__ __forceinline__ void clear() {
-#pragma unroll
-        for (int i = 0; i < NREG; ++i) v.w[i] = 0;
-    }
-    template <bool ALIGNED>
-    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, uint32_t elem) {
-        v = load_wide<NREG, ALIGNED>(rs, 2u * elem);
-    }
+struct StateBytes {
+    static constexpr int kWords = NREG == 1 ? 1 : NREG / 2;
+    uint32_t w[kWords];
 };
 
+// Low bytes of V[k] - m for every half, as state-order bytes; m2 holds m in
+// both halves.  Exact as plain 32-bit arithmetic: V[2j] + 256 V[2j+1] - 257 m2
+// is, modulo 2^32, the sum of the four byte values (each 0..255) at their
+// places.
+template <int NREG>
+__device__ __forceinline__ uint32_t neg257(uint32_t m2) {
+    const uint32_t n = 0u - m2;
+    return NREG == 1 ? n : n + (n << 8);
+}
+template <int NREG>
+__device__ __forceinline__ uint32_t state_word(const uint32_t (&V)[NREG], int j) {
+    return NREG == 1 ? V[0] : V[2 * j] + (V[2 * j + 1 < NREG ? 2 * j + 1 : 0] << 8);
+}
 
-// Stores one lane's step: uint8 slices take the penalty bytes A plus the
-// partner's bytes (each byte sum <= 2 P2 <= 254: no carry between bytes);
-// wide slices take the path values L plus the partner's, as uint16.  `off`
-// is the element offset of the lane's first disparity, kNoWrite for a step
-// outside the line.  For aligned uint8 stores `bias` is the lane's no-write
-// bias; for unaligned ones `ebias` holds one per element, OR-ed (never
-// added) onto the offset so that two biases cannot wrap back into range.
-// Wide stores are guarded by a branch instead: their byte offsets use all
-// 32 bits.
-template <int NREG, bool ALIGNED, bool U8>
-__device__ __forceinline__ void store_step(__amdgpu_buffer_rsrc_t rs, uint32_t off, uint32_t bias,
-                                           bool write, const uint32_t (&ebias)[2 * NREG],
-                                           const uint32_t (&A)[NREG], const uint32_t (&L)[NREG],
-                                           const Partner<NREG, U8>& part) {
-    if constexpr (U8) {
-        constexpr int W = ByteVec<NREG>::kWords;
-        uint32_t pk[W];
-        if constexpr (NREG == 1) {
-            pk[0] = __builtin_amdgcn_perm(0u, A[0], 0x0c0c0200u);
-        } else {
+// state order -> memory order
+template <int NREG>
+__device__ __forceinline__ ByteVec<NREG> to_memory(const StateBytes<NREG>& a) {
+    ByteVec<NREG> o;
+    if constexpr (NREG == 1) {
+        o.w[0] = __builtin_amdgcn_perm(0u, a.w[0], 0x0c0c0200u);
+    } else if constexpr (NREG == 2) {
+        o.w[0] = a.w[0];
+    } else {
 #pragma unroll
-            for (int i = 0; i < W; ++i) pk[i] = __builtin_amdgcn_perm(A[2 * i + 1], A[2 * i], 0x06040200u);
+        for (int i = 0; i < NREG / 4; ++i) {
+            o.w[i] = __builtin_amdgcn_perm(a.w[2 * i + 1], a.w[2 * i], 0x05040100u);
+            o.w[NREG / 4 + i] = __builtin_amdgcn_perm(a.w[2 * i + 1], a.w[2 * i], 0x07060302u);
         }
+    }
+    return o;
+}
+
+// memory order -> state order
+template <int NREG>
+__device__ __forceinline__ StateBytes<NREG> to_state(const ByteVec<NREG>& o) {
+    StateBytes<NREG> a;
+    if constexpr (NREG == 1) {
+        a.w[0] = __builtin_amdgcn_perm(0u, o.w[0], 0x0c010c00u);
+    } else if constexpr (NREG == 2) {
+        a.w[0] = o.w[0];
+    } else {
 #pragma unroll
-        for (int i = 0; i < W; ++i) pk[i] += part.v.w[i];
-        if constexpr (ALIGNED) {
-            const uint32_t o = off | bias;
-            if constexpr (NREG == 1) {
-                __builtin_amdgcn_raw_buffer_store_b16((uint16_t)pk[0], rs, o, 0, 0);
-            } else if constexpr (NREG == 2) {
-                __builtin_amdgcn_raw_buffer_store_b32(pk[0], rs, o, 0, 0);
-            } else if constexpr (NREG == 4) {
-                v2u v;
-                v.x = pk[0];
-                v.y = pk[1];
-                __builtin_amdgcn_raw_buffer_store_b64(v, rs, o, 0, 0);
-            } else {
-                v4u v;
-                v.x = pk[0];
-                v.y = pk[1];
-                v.z = pk[2];
-                v.w = pk[3];
-                __builtin_amdgcn_raw_buffer_store_b128(v, rs, o, 0, 0);
-            }
+        for (int i = 0; i < NREG / 4; ++i) {
+            a.w[2 * i] = __builtin_amdgcn_perm(o.w[NREG / 4 + i], o.w[i], 0x05040100u);
+            a.w[2 * i + 1] = __builtin_amdgcn_perm(o.w[NREG / 4 + i], o.w[i], 0x07060302u);
+        }
+    }
+    return a;
+}
+
+// the same for uint16 values: register k of 2*NREG values in memory order
+template <int NREG>
+__device__ __forceinline__ uint32_t wide_pair(const WideVec<NREG>& c, int k) {
+    if constexpr (NREG == 1) return c.w[0];
+    const int lo = k, hi = NREG + k;
+    return __builtin_amdgcn_perm(c.w[hi >> 1], c.w[lo >> 1],
+                                 (k & 1) ? 0x07060302u : 0x05040100u);
+}
+template <int NREG>
+__device__ __forceinline__ WideVec<NREG> to_memory_wide(const uint32_t (&S)[NREG]) {
+    WideVec<NREG> o;
+    if constexpr (NREG == 1) {
+        o.w[0] = S[0];
+    } else {
+#pragma unroll
+        for (int i = 0; i < NREG / 2; ++i) {
+            o.w[i] = __builtin_amdgcn_perm(S[2 * i + 1], S[2 * i], 0x05040100u);
+            o.w[NREG / 2 + i] = __builtin_amdgcn_perm(S[2 * i + 1], S[2 * i], 0x07060302u);
+        }
+    }
+    return o;
+}
+
+// Stores one lane's 2*NREG slice bytes / uint16 values at element offset
+// `off` (kNoWrite outside the line).  For aligned uint8 stores `bias` is the
+// lane's no-write bias; for unaligned ones `ebias` holds one per element,
+// OR-ed (never added) onto the offset so that two biases cannot wrap back
+// into range.  Wide stores are guarded by a branch instead: their byte
+// offsets use all 32 bits.
+template <int NREG, bool ALIGNED>
+__device__ __forceinline__ void store_bytes(__amdgpu_buffer_rsrc_t rs, uint32_t off, uint32_t bias,
+                                            const uint32_t (&ebias)[2 * NREG], const ByteVec<NREG>& v) {
+    if constexpr (ALIGNED) {
+        const uint32_t o = off | bias;
+        if constexpr (NREG == 1) {
+            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v.w[0], rs, o, 0, kStorePolicy);
+        } else if constexpr (NREG == 2) {
+            __builtin_amdgcn_raw_buffer_store_b32(v.w[0], rs, o, 0, kStorePolicy);
+        } else if constexpr (NREG == 4) {
+            __builtin_amdgcn_raw_buffer_store_b64(v2u{v.w[0], v.w[1]}, rs, o, 0, kStorePolicy);
         } else {
-#pragma unroll
-            for (int e = 0; e < 2 * NREG; ++e)
-                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(pk[e >> 2] >> (8 * (e & 3))), rs,
-                                                     (off | ebias[e]) + (uint32_t)e, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(v4u{v.w[0], v.w[1], v.w[2], v.w[3]}, rs, o, 0, kStorePolicy);
         }
     } else {
-        if (!write || off >= kNoWrite) return;
-        uint32_t s[NREG];
 #pragma unroll
-        for (int k = 0; k < NREG; ++k) s[k] = pk_add(L[k], part.v.w[k]);
-        const uint32_t boff = 2u * off;
-        if constexpr (ALIGNED && NREG == 1) {
-            __builtin_amdgcn_raw_buffer_store_b32(s[0], rs, boff, 0, 0);
-        } else if constexpr (ALIGNED && NREG == 2) {
-            v2u v;
-            v.x = s[0];
-            v.y = s[1];
-            __builtin_amdgcn_raw_buffer_store_b64(v, rs, boff, 0, 0);
-        } else if constexpr (ALIGNED && NREG % 4 == 0) {
-#pragma unroll
-            for (int q = 0; q < NREG / 4; ++q) {
-                v4u v;
-                v.x = s[4 * q];
-                v.y = s[4 * q + 1];
-                v.z = s[4 * q + 2];
-                v.w = s[4 * q + 3];
-                __builtin_amdgcn_raw_buffer_store_b128(v, rs, boff + 16 * q, 0, 0);
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 2 * NREG; ++e)
-                if (ebias[e] == 0)
-                    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(s[e >> 1] >> (16 * (e & 1))), rs,
-                                                          boff + 2 * e, 0, 0);
-        }
+        for (int e = 0; e < 2 * NREG; ++e)
+            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(v.w[e >> 2] >> (8 * (e & 3))), rs,
+                                                 (off | ebias[e]) + (uint32_t)e, 0, 0);
     }
 }
 
-// One step of the recursion for one lane: A (penalty part) and the new L',
-// both as packed uint16 pairs.
-template <int NREG, int LPL, bool PADDED>
-__device__ __forceinline__ void path_step(uint32_t (&Lp)[NREG], const ByteVec<NREG>& c, uint32_t p1x2,
-                                          uint32_t p2x2, const uint32_t (&pad)[NREG], bool first_lane,
-                                          bool last_lane, uint32_t (&A)[NREG]) {
-    // m' over the line
-    uint32_t mm = Lp[0];
+template <int NREG, bool ALIGNED>
+__device__ __forceinline__ void store_wide(__amdgpu_buffer_rsrc_t rs, uint32_t off, bool write,
+                                           const uint32_t (&ebias)[2 * NREG], const WideVec<NREG>& v) {
+    // a slice holds at most 2^31 - 2 values, so this offset is past its end
+    constexpr uint32_t kDrop = 0xFFFFFFFCu;
+    const bool ok = write && off < kNoWrite;
+    const uint32_t boff = 2u * off;
+    if constexpr (ALIGNED && NREG == 1) {
+        __builtin_amdgcn_raw_buffer_store_b32(v.w[0], rs, ok ? boff : kDrop, 0, kStorePolicy);
+    } else if constexpr (ALIGNED && NREG == 2) {
+        __builtin_amdgcn_raw_buffer_store_b64(v2u{v.w[0], v.w[1]}, rs, ok ? boff : kDrop, 0, kStorePolicy);
+    } else if constexpr (ALIGNED && NREG % 4 == 0) {
 #pragma unroll
-    for (int k = 1; k < NREG; ++k) mm = pk_min(mm, Lp[k]);
-    uint32_t m;
-    if constexpr (LPL == 64) m = wave_min_uniform(min(mm & 0xFFFFu, mm >> 16));
-    else m = line_min<LPL>(min(mm & 0xFFFFu, mm >> 16));
+        for (int q = 0; q < NREG / 4; ++q)
+            __builtin_amdgcn_raw_buffer_store_b128(
+                v4u{v.w[4 * q], v.w[4 * q + 1], v.w[4 * q + 2], v.w[4 * q + 3]}, rs,
+                ok ? boff + 16 * q : kDrop, 0, kStorePolicy);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 2 * NREG; ++e)
+            if (ok && ebias[e] == 0)
+                __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(v.w[e >> 1] >> (16 * (e & 1))), rs,
+                                                      boff + 2 * e, 0, 0);
+    }
+}
 
-    // X(d), independent of m'
-    uint32_t Q[NREG];
-    const uint32_t nxt0 = line_next<LPL>(Lp[0], kBig2, last_lane);
-#pragma unroll
-    for (int k = 0; k + 1 < NREG; ++k) Q[k] = pk_min(Lp[k], Lp[k + 1]);
-    Q[NREG - 1] = pk_min(Lp[NREG - 1], nxt0);
-    const uint32_t qprev = line_prev<LPL>(Q[NREG - 1], Lp[0], first_lane);
-    uint32_t X[NREG];
-#pragma unroll
-    for (int k = 0; k < NREG; ++k)
-        X[k] = pk_min(pk_add(pk_shift_in(Q[k], k == 0 ? qprev : Q[k - 1]), p1x2), Lp[k]);
+// Lane constants of the recursion.
+template <int NREG>
+struct LaneConst {
+    uint32_t p1x2, p2x2;
+    uint32_t edge_next, edge_prev;     // OR-ed onto what the neighbour lanes give at a line's edges
+    uint32_t pad[NREG];                // 0, or what lifts a padding disparity above m + P2
+};
 
-    const uint32_t m2 = pk_splat(m);
-    const uint32_t cap = m2 + p2x2;              // no carry crosses the halves: m' + P2 < 2^16
+// V(d) = min(L(d), min(L(d-1), L(d+1)) + P1, m + P2) for every disparity of
+// the lane, from the state L and its line minimum m (m2: in both halves).
+template <int NREG, int LPL, bool NARROW>
+__device__ __forceinline__ void relax(const uint32_t (&L)[NREG], uint32_t m2, const LaneConst<NREG>& lc,
+                                      uint32_t (&V)[NREG]) {
+    const uint32_t cap = m2 + lc.p2x2;           // no carry crosses the halves
+    const uint32_t nx = lane_next<LPL>(L[0]) | lc.edge_next;
+    const uint32_t pv = lane_prev<LPL>(L[NREG - 1]) | lc.edge_prev;
+    const uint32_t below = __builtin_amdgcn_alignbit(L[NREG - 1], pv, 16);    // of register 0
+    const uint32_t above = __builtin_amdgcn_alignbit(nx, L[0], 16);           // of register NREG - 1
 #pragma unroll
     for (int k = 0; k < NREG; ++k) {
-        const uint32_t a = pk_sub(pk_min(X[k], cap), m2);
-        A[k] = a;
-        uint32_t l = pk_add(a, cost_pair<NREG>(c, k));
-        if constexpr (PADDED) l = pk_max(l, pad[k]);
-        Lp[k] = l;
+        const uint32_t nb = pk_min(k == 0 ? below : L[k - 1], k == NREG - 1 ? above : L[k + 1]);
+        V[k] = pk_min3<NARROW>(nb + lc.p1x2, L[k], cap);
+    }
+}
+
+// the next state: V + C (and the padding lift)
+template <int NREG, bool PADDED>
+__device__ __forceinline__ void advance(const uint32_t (&V)[NREG], const ByteVec<NREG>& c,
+                                        const LaneConst<NREG>& lc, uint32_t (&L)[NREG]) {
+#pragma unroll
+    for (int k = 0; k < NREG; ++k) {
+        L[k] = V[k] + byte_pair<NREG>(c, k);
+        if constexpr (PADDED) L[k] += lc.pad[k];
     }
 }
 
@@ -388,57 +462,85 @@ __device__ __forceinline__ void pair_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-// Position of one lane along its line: the element offset of the next step to
-// lay out and, for a diagonal, its column.  A diagonal's steps come with
-// their restart flags: the recursion starts afresh there (the line re-entered
-// at the other border, or the reverse wave's first pixel after its extra
-// steps).  Other lines restart only at the reverse wave's first pixel, which
-// the loop handles itself.
-template <int KIND>
-struct Walker {
-    int t;                 // own pixel index of the next step (< 0: before the line)
-    int n;                 // pixels of the line
-    uint32_t e;            // element offset of pixel t (valid for 0 <= t < n)
-    int x;                 // diagonal: column of pixel t
-    bool wrapped;          // diagonal: pixel t starts a new segment
-    bool restart_first;    // pixel 0 follows extra steps
-    int32_t stride, stride_wrap;
-    int last_x, restart_x, sdx;
+// Orders LDS accesses of the block's waves only: global loads and stores stay
+// in flight across it.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 
-    // offset of the next step, kNoWrite outside the line (CHECKED: the step
-    // may lie outside it); advances
-    template <bool CHECKED>
-    __device__ __forceinline__ uint32_t next(bool& restart) {
-        uint32_t off;
-        if (CHECKED && (t < 0 || t >= n)) {
-            off = kNoWrite;
-            restart = false;
-        } else {
-            off = e;
-            if constexpr (KIND == kDiagonal) {
-                restart = wrapped;
-                wrapped = x == last_x;
-                e += (uint32_t)(wrapped ? stride_wrap : stride);
-                x = wrapped ? restart_x : x + sdx;
-                if (CHECKED && t == 0) restart = restart || restart_first;
-            } else {
-                restart = false;
+// Values of one direction at the K steps of a chunk, as the sum with the other
+// one takes them: penalty bytes in state order, or path values as packed
+// pairs.  put / get carry them through LDS, one row of 64 lanes per step.
+template <int NREG, int K, bool U8>
+struct StepValues {
+    static constexpr int kWords = U8 ? StateBytes<NREG>::kWords : NREG;
+    StateBytes<NREG> a[U8 ? K : 1];
+    uint32_t l[U8 ? 1 : K][NREG];
+    __device__ __forceinline__ void put(uint32_t* row, int lane) const {
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+#pragma unroll
+            for (int i = 0; i < kWords; ++i) row[(j * 64 + lane) * kWords + i] = U8 ? a[U8 ? j : 0].w[U8 ? i : 0] : l[U8 ? 0 : j][U8 ? 0 : i];
+    }
+    __device__ __forceinline__ void get(const uint32_t* row, int lane) {
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+#pragma unroll
+            for (int i = 0; i < kWords; ++i) {
+                if constexpr (U8) a[j].w[i] = row[(j * 64 + lane) * kWords + i];
+                else l[j][i] = row[(j * 64 + lane) * kWords + i];
+            }
+    }
+};
+
+// Position of one lane along its line, laid out a chunk of K steps at a time.
+// A diagonal's line wraps at the left / right border: the recursion restarts
+// there, `left` steps from now.  Most chunks hold no such step in any line of
+// the wave and advance by one stride like the other kinds.
+template <int KIND, int K>
+struct Walker {
+    uint32_t e;            // element offset of the next step
+    int left;              // diagonal: steps before the next restart (0: the next step is one)
+    int32_t stride, wrap;  // wrap: added to e at a restart
+    int width;
+
+    // offsets of the next K steps and their restart flags; true if some line
+    // of the wave restarts among them
+    __device__ __forceinline__ bool next(uint32_t (&offs)[K], bool (&restart)[K]) {
+        if (KIND == kDiagonal && __builtin_amdgcn_ballot_w64(left < K) != 0) {
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                restart[j] = left == 0;
+                e += restart[j] ? (uint32_t)wrap : 0u;
+                left = (restart[j] ? width : left) - 1;
+                offs[j] = e;
                 e += (uint32_t)stride;
             }
+            return true;
         }
-        ++t;
-        return off;
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            offs[j] = e + (uint32_t)(j * stride);
+            restart[j] = false;
+        }
+        e += (uint32_t)(K * stride);
+        left -= K;
+        return false;
     }
 };
 
 // One wave of a line pair, the whole way along.  The offsets of the steps of
 // the next chunk are laid out one chunk ahead and serve its cost loads,
-// partner loads and stores.
-template <int KIND, int NREG, int LPL, int K, bool ALIGNED, bool PADDED, bool U8>
+// its checkpoint and its stores.
+template <int KIND, int NREG, int LPL, int K, bool ALIGNED, bool PADDED, bool U8, bool HELP>
 __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ slice, int q, bool fwd,
-                                         int group) {
+                                         bool helper, int group, uint32_t* __restrict__ lds) {
     constexpr int DPL = 2 * NREG;
     constexpr int LPW = 64 / LPL;
+    constexpr bool NARROW = U8;
+    constexpr int SW = StateBytes<NREG>::kWords;
     const int width = f.width, height = f.height, ndisp = f.ndisp;
     const int lane = threadIdx.x & 63;
     const int sub = lane % LPL;
@@ -449,28 +551,32 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
     const bool d_ok = sub * DPL < ndisp;
     const int d0 = d_ok ? sub * DPL : 0;             // padding lanes read d = 0
     const bool write = line_ok && d_ok;
-    const bool first_lane = sub == 0;
-    const bool last_lane = sub == LPL - 1;
     const int n = KIND == kHorizontal ? width : height;
     const Schedule sch(n, K);
     const int dlt = fwd ? 0 : sch.delta;             // pixel of step s = s - dlt
     const int nchunks = sch.T / K;
     const int c_split = (fwd ? sch.split_fwd : sch.split_rev) / K;
+    // chunks of the longer second half of the two directions
+    const int rounds = nchunks - sch.split_fwd / K;
     // the forward wave's last chunk holds steps past its line's end
     const int c_last_checked = (fwd && sch.delta > 0) ? nchunks - 1 : -1;
 
     const uint32_t vol = (uint32_t)((size_t)width * height * ndisp);
     const __amdgpu_buffer_rsrc_t rc = buffer_rsrc(f.cost, vol);
     const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(slice, U8 ? vol : 2u * vol);
-    const uint32_t p1x2 = pk_splat((uint32_t)f.p1);
-    const uint32_t p2x2 = pk_splat((uint32_t)f.p2);
 
-    uint32_t pad[NREG];
+    LaneConst<NREG> cst;
+    cst.p1x2 = pk_splat((uint32_t)f.p1);
+    cst.p2x2 = pk_splat((uint32_t)f.p2);
+    constexpr uint32_t kEdge = NARROW ? 0x4000u : 0x8000u;
+    cst.edge_next = sub == LPL - 1 ? kEdge : 0u;
+    cst.edge_prev = sub == 0 ? kEdge << 16 : 0u;
+    const uint32_t lift = 255u + (uint32_t)f.p2;
 #pragma unroll
     for (int k = 0; k < NREG; ++k) {
-        const uint32_t lo = (sub * DPL + 2 * k < ndisp) ? 0u : kBig;
-        const uint32_t hi = (sub * DPL + 2 * k + 1 < ndisp) ? 0u : kBig;
-        pad[k] = lo | (hi << 16);
+        const uint32_t lo = (sub * DPL + k < ndisp) ? 0u : lift;
+        const uint32_t hi = (sub * DPL + NREG + k < ndisp) ? 0u : lift;
+        cst.pad[k] = PADDED ? lo | (hi << 16) : 0u;
     }
     uint32_t ebias[DPL];
 #pragma unroll
@@ -494,96 +600,278 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
         const int e = fwd ? lc : (lc + dx * (height - 1)) % width;
         x0 = e < 0 ? e + width : e;
     }
-    Walker<KIND> wk;
-    wk.t = -dlt;
-    wk.n = n;
-    wk.e = ((uint32_t)y0 * (uint32_t)width + (uint32_t)x0) * (uint32_t)ndisp + (uint32_t)d0;
-    wk.x = x0;
-    wk.wrapped = false;
-    wk.restart_first = dlt > 0;
-    wk.stride = (sdy * width + sdx) * ndisp;
-    wk.stride_wrap = (sdy * width + sdx - sdx * width) * ndisp;
-    wk.last_x = sdx > 0 ? width - 1 : 0;
-    wk.restart_x = sdx > 0 ? 0 : width - 1;
-    wk.sdx = sdx;
+    // position of step s of the wave: pixel s - dlt of its line
+    Walker<KIND, K> wk;
+    auto walk_from = [&](int step) {
+        const int t = step - dlt;
+        int xs = x0, ys = y0;
+        if constexpr (KIND == kHorizontal) xs += t * sdx;
+        else ys += t * sdy;
+        if constexpr (KIND == kDiagonal) {
+            xs = (x0 + t * sdx) % width;
+            xs = xs < 0 ? xs + width : xs;
+        }
+        wk.e = ((uint32_t)ys * (uint32_t)width + (uint32_t)xs) * (uint32_t)ndisp + (uint32_t)d0;
+        wk.left = sdx > 0 ? width - xs : xs + 1;
+        wk.stride = (sdy * width + sdx) * ndisp;
+        wk.wrap = -sdx * width * ndisp;
+        wk.width = width;
+    };
 
-    // the next chunk: step offsets, restart flags, cost bytes, partner values
+    // The next chunk: step offsets, restart flags (wrap_n: some line of the
+    // wave restarts in it), cost bytes.  Positions outside the line read as
+    // zero, which keeps a fresh state fresh, so the reverse wave needs no
+    // restart at its first pixel.
     uint32_t offs_n[K];
     bool rst_n[K];
     ByteVec<NREG> cn[K];
-    Partner<NREG, U8> pn[K];
+    bool wrap_n;
+    auto load_next = [&]() {
 #pragma unroll
-    for (int j = 0; j < K; ++j) {
-        offs_n[j] = wk.template next<true>(rst_n[j]);
-        cn[j] = load_bytes<NREG, ALIGNED>(rc, offs_n[j]);
-        pn[j].clear();
+        for (int j = 0; j < K; ++j) cn[j] = load_bytes<NREG, ALIGNED>(rc, offs_n[j]);
+    };
+    // of the last chunk, the forward wave's steps past its line's end
+    auto drop_tail = [&](int c) {
+        if (c == c_last_checked) {
+#pragma unroll
+            for (int j = 0; j < K; ++j) offs_n[j] = j >= K - sch.delta ? kNoWrite : offs_n[j];
+        }
+    };
+    // state of the own recursion, up to an offset common to the line
+    uint32_t L[NREG];
+#pragma unroll
+    for (int k = 0; k < NREG; ++k) L[k] = cst.pad[k];
+    auto restart = [&](uint32_t (&s)[NREG], bool r) {
+#pragma unroll
+        for (int k = 0; k < NREG; ++k) s[k] = r ? cst.pad[k] : s[k];
+    };
+    // one own step: V and the new state; returns m as a pair.  Once per chunk
+    // the offset is taken off.
+    auto own_step = [&](int j, const ByteVec<NREG>& cost, uint32_t (&V)[NREG]) {
+        uint32_t m2 = line_min2<NREG, LPL, NARROW>(L);
+        if (j == 0) {
+#pragma unroll
+            for (int k = 0; k < NREG; ++k) L[k] -= m2;
+            m2 = 0;
+        }
+        relax<NREG, LPL, NARROW>(L, m2, cst, V);
+        advance<NREG, PADDED>(V, cost, cst, L);
+        return m2;
+    };
+
+    // The partner's recursion over a chunk starts from the step it stored, at
+    // the chunk's last pixel, and runs back to the chunk's first.
+    using PartnerSteps = StepValues<NREG, K, U8>;
+    uint32_t P[NREG];
+    ByteVec<NREG> kb;
+    WideVec<NREG> kw;
+    auto load_checkpoint = [&]() {
+        if constexpr (U8) kb = load_bytes<NREG, ALIGNED>(rs, offs_n[K - 1]);
+        else {
+            // twice a no-write offset is inside the slice again
+            kw = load_wide<NREG, ALIGNED>(rs, 2u * offs_n[K - 1]);
+#pragma unroll
+            for (int k = 0; k < NREG; ++k) kw.w[k] = offs_n[K - 1] >= kNoWrite ? 0u : kw.w[k];
+        }
+    };
+    auto partner_first = [&](PartnerSteps& out, const ByteVec<NREG>& cost, const ByteVec<NREG>& kb,
+                             const WideVec<NREG>& kw) {
+        if constexpr (U8) {
+            uint32_t V[NREG];
+            out.a[K - 1] = to_state<NREG>(kb);
+#pragma unroll
+            for (int k = 0; k < NREG; ++k) V[k] = byte_pair<NREG>(kb, k);
+            advance<NREG, PADDED>(V, cost, cst, P);
+        } else {
+#pragma unroll
+            for (int k = 0; k < NREG; ++k) {
+                P[k] = wide_pair<NREG>(kw, k);
+                out.l[K - 1][k] = P[k];
+                // padding may hold anything: bounded, so that the lift cannot overflow
+                if constexpr (PADDED) P[k] = pk_min(P[k], 0x7FFF7FFFu) + cst.pad[k];
+            }
+        }
+    };
+    auto partner_step = [&](int j, PartnerSteps& out, const ByteVec<NREG>& cost) {
+        uint32_t V[NREG];
+        const uint32_t m2 = line_min2<NREG, LPL, NARROW>(P);
+        relax<NREG, LPL, NARROW>(P, m2, cst, V);
+        advance<NREG, PADDED>(V, cost, cst, P);
+        if constexpr (U8) {
+            const uint32_t nm = neg257<NREG>(m2);
+#pragma unroll
+            for (int i = 0; i < SW; ++i) out.a[j].w[i] = state_word<NREG>(V, i) + nm;
+        } else {
+#pragma unroll
+            for (int k = 0; k < NREG; ++k) out.l[j][k] = P[k] - m2;
+        }
+    };
+    if constexpr (HELP) {
+        if (helper) {
+            // the partner's steps of every chunk of the second half, through
+            // LDS to the wave that walks it
+            walk_from(c_split * K);
+            pair_barrier();
+            if (c_split < nchunks) {
+                wrap_n = wk.next(offs_n, rst_n);
+                drop_tail(c_split);
+                load_next();
+                load_checkpoint();
+            }
+            for (int i = 0; i < rounds; ++i) {
+                const int c = c_split + i;
+                if (c < nchunks) {
+                    ByteVec<NREG> cur[K];
+                    bool rst[K];
+                    const bool w = wrap_n;
+#pragma unroll
+                    for (int j = 0; j < K; ++j) {
+                        cur[j] = cn[j];
+                        rst[j] = rst_n[j];
+                    }
+                    const ByteVec<NREG> kb0 = kb;
+                    const WideVec<NREG> kw0 = kw;
+                    if (c + 1 < nchunks) {
+                        wrap_n = wk.next(offs_n, rst_n);
+                        drop_tail(c + 1);
+                        load_next();
+                        load_checkpoint();
+                    }
+                    auto steps = [&](auto wraps) {
+                        constexpr bool WRAPS = decltype(wraps)::value;
+                        PartnerSteps out;
+                        partner_first(out, cur[K - 1], kb0, kw0);
+#pragma unroll
+                        for (int j = K - 2; j >= 0; --j) {
+                            if constexpr (WRAPS) restart(P, rst[j + 1]);
+                            partner_step(j, out, cur[j]);
+                        }
+                        out.put(lds + (i & 1) * (K * 64 * PartnerSteps::kWords), lane);
+                    };
+                    if (KIND == kDiagonal && w) steps(std::true_type{});
+                    else steps(std::false_type{});
+                }
+                lds_barrier();
+            }
+            return;
+        }
     }
 
-    // L' of the previous pixel; padding at a line's start
-    uint32_t Lp[NREG];
+    walk_from(0);
+    wrap_n = wk.next(offs_n, rst_n);
 #pragma unroll
-    for (int k = 0; k < NREG; ++k) Lp[k] = pad[k];
+    for (int j = 0; j < K; ++j) offs_n[j] = j < dlt ? kNoWrite : offs_n[j];
+    drop_tail(0);
+    load_next();
 
-    // one chunk; CHECK: some step of it may restart the recursion
-    auto chunk = [&](int c, auto check) {
-        constexpr bool CHECK = decltype(check)::value;
-        uint32_t offs[K];
+    // ---- first half: only the first step of every chunk is stored.  The
+    // next chunk's loads are issued as this chunk's bytes are used up.
+    auto first_half = [&](auto wraps) {
+        constexpr bool WRAPS = decltype(wraps)::value;
+        const uint32_t off0 = offs_n[0];
         bool rst[K];
-        ByteVec<NREG> cur[K];
-        Partner<NREG, U8> pc[K];
+#pragma unroll
+        for (int j = 0; j < K; ++j) rst[j] = rst_n[j];
+        wrap_n = wk.next(offs_n, rst_n);
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            if constexpr (WRAPS) restart(L, rst[j]);
+            uint32_t V[NREG];
+            own_step(j, cn[j], V);
+            cn[j] = load_bytes<NREG, ALIGNED>(rc, offs_n[j]);
+            if (j == 0) {
+                if constexpr (U8) {
+                    StateBytes<NREG> a;
+#pragma unroll
+                    for (int i = 0; i < SW; ++i) a.w[i] = state_word<NREG>(V, i);
+                    store_bytes<NREG, ALIGNED>(rs, off0, lane_bias, ebias, to_memory<NREG>(a));
+                } else {
+                    store_wide<NREG, ALIGNED>(rs, off0, write, ebias, to_memory_wide<NREG>(L));
+                }
+            }
+        }
+    };
+    for (int c = 0; c < c_split; ++c) {
+        if (KIND == kDiagonal && wrap_n) first_half(std::true_type{});
+        else first_half(std::false_type{});
+    }
+    if (c_split > 0 && c_split == c_last_checked) {
+        drop_tail(c_split);
+        load_next();
+    }
+    pair_barrier();
+    if (!HELP && c_split == nchunks) return;
+
+    // ---- second half -----------------------------------------------------------
+    // one own step; the sum of both directions goes out
+    auto own_out = [&](int j, const ByteVec<NREG>& cost, const PartnerSteps& p, uint32_t off) {
+        uint32_t V[NREG];
+        const uint32_t m2 = own_step(j, cost, V);
+        if constexpr (U8) {
+            const uint32_t nm = neg257<NREG>(m2);
+            StateBytes<NREG> a;
+#pragma unroll
+            for (int i = 0; i < SW; ++i) a.w[i] = state_word<NREG>(V, i) + (p.a[j].w[i] + nm);
+            store_bytes<NREG, ALIGNED>(rs, off, lane_bias, ebias, to_memory<NREG>(a));
+        } else {
+            uint32_t S[NREG];
+#pragma unroll
+            for (int k = 0; k < NREG; ++k) S[k] = L[k] + (p.l[j][k] - m2);
+            store_wide<NREG, ALIGNED>(rs, off, write, ebias, to_memory_wide<NREG>(S));
+        }
+    };
+
+    if constexpr (!HELP) load_checkpoint();
+    uint32_t offs[K];
+    bool rst[K];
+    ByteVec<NREG> cur[K];
+    PartnerSteps pa;
+    auto second_half = [&](int c, auto wraps) {
+        constexpr bool WRAPS = decltype(wraps)::value;
+        if constexpr (HELP) {
+            pa.get(lds + ((c - c_split) & 1) * (K * 64 * PartnerSteps::kWords), lane);
+        } else {
+            partner_first(pa, cur[K - 1], kb, kw);
+            if (c + 1 < nchunks) load_checkpoint();
+#pragma unroll
+            for (int j = K - 2; j >= 0; --j) {
+                if constexpr (WRAPS) restart(P, rst[j + 1]);
+                partner_step(j, pa, cur[j]);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            if constexpr (WRAPS) restart(L, rst[j]);
+            own_out(j, cur[j], pa, offs[j]);
+        }
+    };
+    // Loads and stores share one in-order counter, and the wait at the loop's
+    // top has to hold on its first round too: without a chunk's worth of
+    // stores behind the first loads it would wait for the last round's stores
+    // on every round.  The range check of an empty buffer drops these.
+    const __amdgpu_buffer_rsrc_t nowhere = buffer_rsrc(slice, 0);
+#pragma unroll
+    for (int j = 0; j < K; ++j) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)0, nowhere, 4 * j, 0, 0);
+    for (int c = c_split; c < nchunks; ++c) {
+        const bool w = wrap_n;
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             offs[j] = offs_n[j];
             rst[j] = rst_n[j];
             cur[j] = cn[j];
-            pc[j] = pn[j];
-        }
-        if (c == c_split) {
-            // the other wave has written the pixels this one completes
-            pair_barrier();
-#pragma unroll
-            for (int j = 0; j < K; ++j) pc[j].template load<ALIGNED>(rs, offs[j]);
         }
         if (c + 1 < nchunks) {
-            if (c + 1 == c_last_checked) {
-#pragma unroll
-                for (int j = 0; j < K; ++j) offs_n[j] = wk.template next<true>(rst_n[j]);
-            } else {
-#pragma unroll
-                for (int j = 0; j < K; ++j) offs_n[j] = wk.template next<false>(rst_n[j]);
-            }
-#pragma unroll
-            for (int j = 0; j < K; ++j) cn[j] = load_bytes<NREG, ALIGNED>(rc, offs_n[j]);
-            if (c >= c_split) {
-#pragma unroll
-                for (int j = 0; j < K; ++j) pn[j].template load<ALIGNED>(rs, offs_n[j]);
-            }
+            wrap_n = wk.next(offs_n, rst_n);
+            drop_tail(c + 1);
+            load_next();
         }
-#pragma unroll
-        for (int j = 0; j < K; ++j) {
-            if constexpr (CHECK && KIND == kDiagonal) {
-                // a restart is rare; skip the selects on the other steps
-                if (__builtin_amdgcn_ballot_w64(rst[j])) {
-#pragma unroll
-                    for (int k = 0; k < NREG; ++k) Lp[k] = rst[j] ? pad[k] : Lp[k];
-                }
-            } else if constexpr (CHECK) {
-                // the reverse wave's first pixel after its extra steps
-                if (j == dlt) {
-#pragma unroll
-                    for (int k = 0; k < NREG; ++k) Lp[k] = pad[k];
-                }
-            }
-            uint32_t A[NREG];
-            path_step<NREG, LPL, PADDED>(Lp, cur[j], p1x2, p2x2, pad, first_lane, last_lane, A);
-            store_step<NREG, ALIGNED, U8>(rs, offs[j], lane_bias, write, ebias, A, Lp, pc[j]);
-        }
-    };
-    for (int c = 0; c < nchunks; ++c) {
-        if (KIND == kDiagonal || (c == 0 && dlt > 0)) chunk(c, std::true_type{});
-        else chunk(c, std::false_type{});
+        if constexpr (HELP) lds_barrier();
+        if (KIND == kDiagonal && w) second_half(c, std::true_type{});
+        else second_half(c, std::false_type{});
     }
-    if (c_split == nchunks) pair_barrier();
+    if constexpr (HELP) {
+        for (int i = nchunks - c_split; i < rounds; ++i) lds_barrier();
+    }
 }
 
 // Block lb of the path pass of one frame: pair q, line groups 2g and 2g + 1;
@@ -591,16 +879,15 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
 // one.
 template <int NH, int LH, int NO, int LO, bool ALH, bool PDH, bool ALO, bool PDO, bool U8>
 __device__ __forceinline__ void paths_block(const Frame& f, int lb) {
-    // steps per chunk: enough to cover a memory round trip, few enough to
-    // keep two chunks of cost bytes and partner values in registers
-    constexpr int KH = NH == 1 ? kStepsH1 : kStepsH2;
-    constexpr int KO = NO <= 4 ? kStepsO4 : kStepsO8;
+    constexpr int KH = kStepsH, KO = kStepsO;
+    constexpr PathLayout kLayout = kPathLayouts[SGM_PATH_LAYOUT];
+    constexpr bool HELPH = kLayout.help_h, HELPO = kLayout.help_o;
     const int npairs = f.npaths / 2;
     if (f.paths_fill_keys) {
         // the D^R key map of the selection that follows starts at "no
         // candidate"; every block clears an equal share of it
         int nb = 0;
-        for (int q = 0; q < npairs; ++q) nb += pair_blocks(q, f.width, f.height, LH, LO);
+        for (int q = 0; q < npairs; ++q) nb += pair_blocks(q, f.width, f.height, kLayout);
         const size_t n = (size_t)f.width * f.height;
         const size_t per = (n + nb - 1) / nb;
         const size_t e1 = min(n, (size_t)(lb + 1) * per);
@@ -608,21 +895,31 @@ __device__ __forceinline__ void paths_block(const Frame& f, int lb) {
     }
     int q = 0, start = 0;
     for (; q < npairs - 1; ++q) {
-        const int nb = pair_blocks(q, f.width, f.height, LH, LO);
+        const int nb = pair_blocks(q, f.width, f.height, kLayout);
         if (lb < start + nb) break;
         start += nb;
     }
-    const int group = 2 * (lb - start) + ((threadIdx.x >> 6) & 1);
-    const bool fwd = threadIdx.x < 128;
+    // the same for all lanes of a wave, and known to be: the loops and branches
+    // below stay scalar
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int lb0 = lb - start;
     uint8_t* slice = f.slices + (size_t)q * f.slice_stride * (U8 ? 1 : 2);
+    constexpr int kLdsH = HELPH ? 2 * KH * 64 * StepValues<NH, KH, U8>::kWords : 0;
+    constexpr int kLdsO = HELPO ? 2 * KO * 64 * StepValues<NO, KO, U8>::kWords : 0;
+    constexpr int kLds = kLdsH > kLdsO ? kLdsH : kLdsO;
+    __shared__ __align__(16) uint32_t lds[kLds > 0 ? 2 * kLds : 1];
+    const bool help = q == 0 ? HELPH : HELPO;
+    const bool fwd = help ? (wave & 1) == 0 : wave < 2;
+    const int group = help ? lb0 : 2 * lb0 + (wave & 1);
+    uint32_t* mine = lds + (fwd ? 0 : kLds);
     if (q == 0) {
         __builtin_amdgcn_s_setprio(2);
-        run_wave<kHorizontal, NH, LH, KH, ALH, PDH, U8>(f, slice, q, fwd, group);
+        run_wave<kHorizontal, NH, LH, KH, ALH, PDH, U8, HELPH>(f, slice, q, fwd, wave >= 2, group, mine);
         __builtin_amdgcn_s_setprio(0);
     } else if (q == 1) {
-        run_wave<kVertical, NO, LO, KO, ALO, PDO, U8>(f, slice, q, fwd, group);
+        run_wave<kVertical, NO, LO, KO, ALO, PDO, U8, HELPO>(f, slice, q, fwd, wave >= 2, group, mine);
     } else {
-        run_wave<kDiagonal, NO, LO, KO, ALO, PDO, U8>(f, slice, q, fwd, group);
+        run_wave<kDiagonal, NO, LO, KO, ALO, PDO, U8, HELPO>(f, slice, q, fwd, wave >= 2, group, mine);
     }
 }
 
@@ -703,13 +1000,6 @@ hipError_t launch_paths_worklist(const WorkList& wl, int ndisp, bool u8, int nbl
 #endif
 
 }  // namespace
-
-#ifndef SGM_PATH_LAYOUT
-#error "paths.hip is compiled once per lane layout: -DSGM_PATH_LAYOUT=<index>"
-#endif
-#if !defined(SGM_PATH_PART) || (SGM_PATH_PART != 0 && SGM_PATH_PART != 1)
-#error "paths.hip is compiled in two parts: -DSGM_PATH_PART=0 (single frame) or 1 (work list)"
-#endif
 
 #if SGM_PATH_PART == 0
 template <>

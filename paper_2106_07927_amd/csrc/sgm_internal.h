@@ -256,13 +256,19 @@ __host__ __device__ inline int fill_blocks(size_t n) { return (int)((n + kFillCh
 struct PathLayout {
     int nreg_h, lpl_h;    // horizontal lines
     int nreg_o, lpl_o;    // vertical and diagonal lines
+    bool help_h, help_o;  // two waves per line group walk the partner's steps for the other two
+    bool stream;          // nontemporal slice stores
 };
 
 // Every layout the library builds (paths.hip is compiled once per entry).
 constexpr int kNumPathLayouts = 12;
 constexpr PathLayout kPathLayouts[kNumPathLayouts] = {
-    {1, 1, 1, 1}, {1, 2, 2, 1}, {1, 4, 4, 1}, {1, 8, 4, 2}, {1, 16, 4, 4}, {1, 32, 4, 8},
-    {2, 16, 4, 8}, {1, 64, 4, 16}, {2, 32, 4, 16}, {1, 64, 8, 8}, {2, 64, 8, 16}, {4, 32, 8, 16},
+    {1, 1, 1, 1, true, false, false},    {1, 2, 2, 1, true, false, false},
+    {1, 4, 4, 1, true, false, false},    {1, 8, 4, 2, true, false, false},
+    {1, 16, 4, 4, true, false, false},   {2, 16, 4, 8, true, true, false},
+    {2, 16, 4, 8, false, false, false},  {2, 32, 4, 16, true, false, false},
+    {2, 32, 8, 8, true, false, false},   {4, 16, 8, 8, false, false, true},
+    {4, 32, 8, 16, true, false, true},   {4, 32, 8, 16, false, false, true},
 };
 
 // The path pass for layout kPathLayouts[ID] (paths.hip compiled per layout,
@@ -304,14 +310,15 @@ __host__ __device__ inline void pair_dir(int q, int* dx, int* dy) {
 
 __host__ __device__ inline int pair_lines(int q, int width, int height) { return q == 0 ? height : width; }
 
-// Blocks of pair q in the path pass: one block (the forward and the reverse
-// waves of two line groups) per two waves' worth of lines.
-__host__ __device__ inline int pair_blocks(int q, int width, int height, int lpl_h, int lpl_o) {
-    const int lpb = 2 * (64 / (q == 0 ? lpl_h : lpl_o));
+// Blocks of pair q in the path pass: a block holds the forward and the reverse
+// waves of two line groups, or of one line group and their two helpers.
+__host__ __device__ inline int pair_blocks(int q, int width, int height, const PathLayout& l) {
+    const bool help = q == 0 ? l.help_h : l.help_o;
+    const int lpb = (help ? 1 : 2) * (64 / (q == 0 ? l.lpl_h : l.lpl_o));
     return (pair_lines(q, width, height) + lpb - 1) / lpb;
 }
 int path_variants(int ndisp);                       // number of variants (>= 1)
-int default_variant(int width, int height, int ndisp);
+int default_variant(int width, int height, int ndisp, int npaths);
 PathLayout path_layout(int ndisp, int variant);
 int path_blocks(int width, int height, int ndisp, int npaths, int variant);
 // blocks of the horizontal directions, which come first in a frame's block order

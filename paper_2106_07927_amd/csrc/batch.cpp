@@ -225,7 +225,14 @@ size_t build_layout(const sgm_pair* pairs, int32_t n, const sgm_params* p, const
         off += align256((L.frames.size() + 1) * sizeof(int32_t));
         if (L.stage == kPaths) {
             size_t items = 0;
-            for (int k : L.frames) items += stage_blocks(kPaths, (*frames)[k]);
+            for (int k : L.frames) {
+                // room for any variant's blocks: the size does not depend on the table
+                const Frame& f = (*frames)[k];
+                int most = 0;
+                for (int v = 0; v < path_variants(f.ndisp); ++v)
+                    most = std::max(most, path_blocks(f.width, f.height, f.ndisp, f.npaths, v));
+                items += most;
+            }
             L.items_off = off;
             off += align256(2 * items * sizeof(int32_t));
         }

@@ -112,7 +112,11 @@ int path_layout_id(int ndisp, int variant) {
     if (ndisp <= 16) return 3;
     if (ndisp <= 32) return 4;
     if (ndisp <= 64) return 5 + (variant == 1);
-    if (ndisp <= 128) return 7 + (variant == 1 || variant == 2 ? variant : 0);
+    // a D that cuts the 16 disparities of a lane in two: eight per lane instead
+    // (803x397, D = 100, path pass alone: 111 us against 186; the kernels with
+    // 16 per lane would not fit two waves on a SIMD)
+    if (ndisp <= 128) return 7 + (ndisp % 16 == 0 && (variant == 1 || variant == 2) ? variant : 0);
+    if (ndisp % 16 != 0) return 12;
     return 10 + (variant == 1);
 }
 }  // namespace
@@ -167,6 +171,7 @@ hipError_t launch_paths_any(const Frame* one, const WorkList* wl, int ndisp, int
     SGM_CASE(9)
     SGM_CASE(10)
     SGM_CASE(11)
+    SGM_CASE(12)
 #undef SGM_CASE
     return hipErrorInvalidValue;
 }

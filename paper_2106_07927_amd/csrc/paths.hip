@@ -61,6 +61,12 @@
 // neighbour terms.  Disparities beyond D (padding) are lifted by 255 + P2 in
 // every step: as neighbours they never come below m + P2, and m never is one.
 //
+// Where D cuts a lane's disparities (RAGGED) the accesses stay whole vectors,
+// at any byte alignment; only the lane that holds d = D - 1 stores its values
+// in parts, and only the chunk with the line's last pixel is loaded byte by
+// byte, since there a vector may reach past the volume (803x397, D = 100:
+// 594 us with byte accesses in the first design, 310 in this one, now 111).
+//
 // Memory.  Loads run a chunk ahead.  Cost and checkpoint loads and the slice
 // stores go through raw buffer resources: offsets past the volume read as
 // zero and stores there are dropped, so positions beyond a line need no
@@ -195,47 +201,51 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(const void* base, 
                                              kRawBufferWord3);
 }
 
-// 2*NREG bytes at byte offset `off` (out of range: zero)
-template <int NREG, bool ALIGNED>
+// 2*NREG bytes at byte offset `off` (out of range: zero).  Any alignment: the
+// hardware takes unaligned buffer accesses.
+template <int NREG>
 __device__ __forceinline__ ByteVec<NREG> load_bytes(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
     ByteVec<NREG> c;
-    if constexpr (ALIGNED) {
-        if constexpr (NREG == 1) {
-            c.w[0] = __builtin_amdgcn_raw_buffer_load_b16(rs, off, 0, 0);
-        } else if constexpr (NREG == 2) {
-            c.w[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0);
-        } else if constexpr (NREG == 4) {
-            const v2u v = __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
-            c.w[0] = v.x;
-            c.w[1] = v.y;
-        } else {
-            const v4u v = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
-            c.w[0] = v.x;
-            c.w[1] = v.y;
-            c.w[2] = v.z;
-            c.w[3] = v.w;
-        }
+    if constexpr (NREG == 1) {
+        c.w[0] = __builtin_amdgcn_raw_buffer_load_b16(rs, off, 0, 0);
+    } else if constexpr (NREG == 2) {
+        c.w[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0);
+    } else if constexpr (NREG == 4) {
+        const v2u v = __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
+        c.w[0] = v.x;
+        c.w[1] = v.y;
     } else {
-#pragma unroll
-        for (int i = 0; i < ByteVec<NREG>::kWords; ++i) c.w[i] = 0;
-#pragma unroll
-        for (int e = 0; e < 2 * NREG; ++e)
-            c.w[e >> 2] |= (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(rs, off + e, 0, 0) << (8 * (e & 3));
+        const v4u v = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+        c.w[0] = v.x;
+        c.w[1] = v.y;
+        c.w[2] = v.z;
+        c.w[3] = v.w;
     }
     return c;
 }
 
+// the same byte by byte, each checked by itself: where the 2*NREG bytes may
+// reach past the volume's end
+template <int NREG>
+__device__ __forceinline__ ByteVec<NREG> load_bytes_each(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
+    ByteVec<NREG> c{};
+#pragma unroll
+    for (int e = 0; e < 2 * NREG; ++e)
+        c.w[e >> 2] |= (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(rs, off + e, 0, 0) << (8 * (e & 3));
+    return c;
+}
+
 // 2*NREG uint16 values at byte offset `off` (out of range: zero)
-template <int NREG, bool ALIGNED>
+template <int NREG>
 __device__ __forceinline__ WideVec<NREG> load_wide(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
     WideVec<NREG> v;
-    if constexpr (ALIGNED && NREG == 1) {
+    if constexpr (NREG == 1) {
         v.w[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0);
-    } else if constexpr (ALIGNED && NREG == 2) {
+    } else if constexpr (NREG == 2) {
         const v2u a = __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
         v.w[0] = a.x;
         v.w[1] = a.y;
-    } else if constexpr (ALIGNED && NREG % 4 == 0) {
+    } else {
 #pragma unroll
         for (int q = 0; q < NREG / 4; ++q) {
             const v4u a = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16 * q, 0, 0);
@@ -244,12 +254,17 @@ __device__ __forceinline__ WideVec<NREG> load_wide(__amdgpu_buffer_rsrc_t rs, ui
             v.w[4 * q + 2] = a.z;
             v.w[4 * q + 3] = a.w;
         }
-    } else {
-#pragma unroll
-        for (int k = 0; k < NREG; ++k)
-            v.w[k] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, off + 4 * k, 0, 0) |
-                     ((uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, off + 4 * k + 2, 0, 0) << 16);
     }
+    return v;
+}
+
+template <int NREG>
+__device__ __forceinline__ WideVec<NREG> load_wide_each(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
+    WideVec<NREG> v;
+#pragma unroll
+    for (int k = 0; k < NREG; ++k)
+        v.w[k] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, off + 4 * k, 0, 0) |
+                 ((uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, off + 4 * k + 2, 0, 0) << 16);
     return v;
 }
 
@@ -349,72 +364,113 @@ __device__ __forceinline__ WideVec<NREG> to_memory_wide(const uint32_t (&S)[NREG
     return o;
 }
 
-// Stores one lane's 2*NREG slice bytes / uint16 values at element offset
-// `off` (kNoWrite outside the line).  For aligned uint8 stores `bias` is the
-// lane's no-write bias; for unaligned ones `ebias` holds one per element,
-// OR-ed (never added) onto the offset so that two biases cannot wrap back
-// into range.  Wide stores are guarded by a branch instead: their byte
-// offsets use all 32 bits.
-template <int NREG, bool ALIGNED>
-__device__ __forceinline__ void store_bytes(__amdgpu_buffer_rsrc_t rs, uint32_t off, uint32_t bias,
-                                            const uint32_t (&ebias)[2 * NREG], const ByteVec<NREG>& v) {
-    if constexpr (ALIGNED) {
-        const uint32_t o = off | bias;
-        if constexpr (NREG == 1) {
-            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v.w[0], rs, o, 0, kStorePolicy);
-        } else if constexpr (NREG == 2) {
-            __builtin_amdgcn_raw_buffer_store_b32(v.w[0], rs, o, 0, kStorePolicy);
-        } else if constexpr (NREG == 4) {
-            __builtin_amdgcn_raw_buffer_store_b64(v2u{v.w[0], v.w[1]}, rs, o, 0, kStorePolicy);
-        } else {
-            __builtin_amdgcn_raw_buffer_store_b128(v4u{v.w[0], v.w[1], v.w[2], v.w[3]}, rs, o, 0, kStorePolicy);
-        }
+// What a lane stores of its 2*NREG slice values: all of them (`full` is 0), or
+// with RAGGED (D no multiple of 2*NREG) the lane that holds d = D - 1 stores
+// its first D % (2*NREG) = r values, in parts of 8, 4, 2 and 1 values
+// (part[k] is 0 where the lane stores the part of 8 >> k).  Any other of these
+// is kNoWrite, and OR-ed onto the offset.
+struct StoreLanes {
+    uint32_t full, part[4];
+    int r;
+};
+
+// One word of `w` by an index that is the same for the whole wave: bitwise,
+// since a choice by comparisons becomes an indexed load from scratch memory.
+template <int N>
+__device__ __forceinline__ uint32_t pick(const uint32_t (&w)[N], int i) {
+    if constexpr (N == 1) {
+        return w[0];
     } else {
+        const uint32_t up = (i & (N / 2)) ? 0xFFFFFFFFu : 0u;
+        uint32_t h[N / 2];
 #pragma unroll
-        for (int e = 0; e < 2 * NREG; ++e)
-            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(v.w[e >> 2] >> (8 * (e & 3))), rs,
-                                                 (off | ebias[e]) + (uint32_t)e, 0, 0);
+        for (int k = 0; k < N / 2; ++k) h[k] = (w[k + N / 2] & up) | (w[k] & ~up);
+        return pick(h, i);
     }
 }
 
-template <int NREG, bool ALIGNED>
-__device__ __forceinline__ void store_wide(__amdgpu_buffer_rsrc_t rs, uint32_t off, bool write,
-                                           const uint32_t (&ebias)[2 * NREG], const WideVec<NREG>& v) {
-    // a slice holds at most 2^31 - 2 values, so this offset is past its end
-    constexpr uint32_t kDrop = 0xFFFFFFFCu;
-    const bool ok = write && off < kNoWrite;
-    const uint32_t boff = 2u * off;
-    if constexpr (ALIGNED && NREG == 1) {
-        __builtin_amdgcn_raw_buffer_store_b32(v.w[0], rs, ok ? boff : kDrop, 0, kStorePolicy);
-    } else if constexpr (ALIGNED && NREG == 2) {
-        __builtin_amdgcn_raw_buffer_store_b64(v2u{v.w[0], v.w[1]}, rs, ok ? boff : kDrop, 0, kStorePolicy);
-    } else if constexpr (ALIGNED && NREG % 4 == 0) {
+// Stores one lane's slice bytes at element offset `off` (kNoWrite outside the
+// line).
+template <int NREG, bool RAGGED>
+__device__ __forceinline__ void store_bytes(__amdgpu_buffer_rsrc_t rs, uint32_t off, const StoreLanes& sl,
+                                            const ByteVec<NREG>& v) {
+    const uint32_t o = off | sl.full;
+    if constexpr (NREG == 1) {
+        __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v.w[0], rs, o, 0, kStorePolicy);
+    } else if constexpr (NREG == 2) {
+        __builtin_amdgcn_raw_buffer_store_b32(v.w[0], rs, o, 0, kStorePolicy);
+    } else if constexpr (NREG == 4) {
+        __builtin_amdgcn_raw_buffer_store_b64(v2u{v.w[0], v.w[1]}, rs, o, 0, kStorePolicy);
+    } else {
+        __builtin_amdgcn_raw_buffer_store_b128(v4u{v.w[0], v.w[1], v.w[2], v.w[3]}, rs, o, 0, kStorePolicy);
+    }
+    if constexpr (RAGGED) {
+        constexpr int W = ByteVec<NREG>::kWords;
+        const int r = sl.r;
+        if constexpr (NREG == 8)
+            __builtin_amdgcn_raw_buffer_store_b64(v2u{v.w[0], v.w[W > 1 ? 1 : 0]}, rs, off | sl.part[0], 0, 0);
+        if constexpr (NREG >= 4)
+            __builtin_amdgcn_raw_buffer_store_b32(pick(v.w, (r & 8) >> 2), rs, (off | sl.part[1]) + (r & 8), 0, 0);
+        if (r & 3) {
+            const uint32_t last = pick(v.w, r >> 2);
+            if constexpr (NREG >= 2)
+                __builtin_amdgcn_raw_buffer_store_b16((uint16_t)last, rs, (off | sl.part[2]) + (r & 12), 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(last >> (8 * (r & 2))), rs,
+                                                 (off | sl.part[3]) + (r & 14), 0, 0);
+        }
+    }
+}
+
+// The same for uint16 values; their byte offsets use all 32 bits, so a value
+// that must not be stored gets an offset past any slice (a slice holds at
+// most 2^31 - 2 values).
+template <int NREG, bool RAGGED>
+__device__ __forceinline__ void store_wide(__amdgpu_buffer_rsrc_t rs, uint32_t off, const StoreLanes& sl,
+                                           const WideVec<NREG>& v) {
+    auto at = [&](uint32_t bias, uint32_t add) { return (off | bias) < kNoWrite ? 2u * off + add : 0xFFFFFFFCu; };
+    if constexpr (NREG == 1) {
+        __builtin_amdgcn_raw_buffer_store_b32(v.w[0], rs, at(sl.full, 0), 0, kStorePolicy);
+    } else if constexpr (NREG == 2) {
+        __builtin_amdgcn_raw_buffer_store_b64(v2u{v.w[0], v.w[1]}, rs, at(sl.full, 0), 0, kStorePolicy);
+    } else {
 #pragma unroll
         for (int q = 0; q < NREG / 4; ++q)
             __builtin_amdgcn_raw_buffer_store_b128(
-                v4u{v.w[4 * q], v.w[4 * q + 1], v.w[4 * q + 2], v.w[4 * q + 3]}, rs,
-                ok ? boff + 16 * q : kDrop, 0, kStorePolicy);
-    } else {
-#pragma unroll
-        for (int e = 0; e < 2 * NREG; ++e)
-            if (ok && ebias[e] == 0)
-                __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(v.w[e >> 1] >> (16 * (e & 1))), rs,
-                                                      boff + 2 * e, 0, 0);
+                v4u{v.w[4 * q], v.w[4 * q + 1], v.w[4 * q + 2], v.w[4 * q + 3]}, rs, at(sl.full, 16 * q), 0,
+                kStorePolicy);
+    }
+    if constexpr (RAGGED) {
+        const int r = sl.r;
+        if constexpr (NREG == 8)
+            __builtin_amdgcn_raw_buffer_store_b128(v4u{v.w[0], v.w[1], v.w[2], v.w[3]}, rs, at(sl.part[0], 0), 0, 0);
+        if constexpr (NREG >= 4) {
+            __builtin_amdgcn_raw_buffer_store_b64(v2u{pick(v.w, (r & 8) >> 1), pick(v.w, ((r & 8) >> 1) + 1)}, rs,
+                                                  at(sl.part[1], 2 * (r & 8)), 0, 0);
+        }
+        if (r & 3) {
+            const uint32_t last = pick(v.w, r >> 1);          // holds value r & ~1, ...
+            if constexpr (NREG >= 2)
+                __builtin_amdgcn_raw_buffer_store_b32(pick(v.w, (r & 12) >> 1), rs, at(sl.part[2], 2 * (r & 12)),
+                                                      0, 0);
+            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)last, rs, at(sl.part[3], 2 * (r & 14)), 0, 0);
+        }
     }
 }
 
-// Lane constants of the recursion.
-template <int NREG>
+// Lane constants of the recursion.  Unless RAGGED, a lane is padding as a whole
+// or not at all.
+template <int NREG, bool RAGGED>
 struct LaneConst {
     uint32_t p1x2, p2x2;
     uint32_t edge_next, edge_prev;     // OR-ed onto what the neighbour lanes give at a line's edges
-    uint32_t pad[NREG];                // 0, or what lifts a padding disparity above m + P2
+    uint32_t pad[RAGGED ? NREG : 1];   // 0, or what lifts a padding disparity above m + P2
+    __device__ __forceinline__ uint32_t lift(int k) const { return pad[RAGGED ? k : 0]; }
 };
 
 // V(d) = min(L(d), min(L(d-1), L(d+1)) + P1, m + P2) for every disparity of
 // the lane, from the state L and its line minimum m (m2: in both halves).
-template <int NREG, int LPL, bool NARROW>
-__device__ __forceinline__ void relax(const uint32_t (&L)[NREG], uint32_t m2, const LaneConst<NREG>& lc,
+template <int NREG, int LPL, bool NARROW, bool RAGGED>
+__device__ __forceinline__ void relax(const uint32_t (&L)[NREG], uint32_t m2, const LaneConst<NREG, RAGGED>& lc,
                                       uint32_t (&V)[NREG]) {
     const uint32_t cap = m2 + lc.p2x2;           // no carry crosses the halves
     const uint32_t nx = lane_next<LPL>(L[0]) | lc.edge_next;
@@ -429,13 +485,13 @@ __device__ __forceinline__ void relax(const uint32_t (&L)[NREG], uint32_t m2, co
 }
 
 // the next state: V + C (and the padding lift)
-template <int NREG, bool PADDED>
+template <int NREG, bool PADDED, bool RAGGED>
 __device__ __forceinline__ void advance(const uint32_t (&V)[NREG], const ByteVec<NREG>& c,
-                                        const LaneConst<NREG>& lc, uint32_t (&L)[NREG]) {
+                                        const LaneConst<NREG, RAGGED>& lc, uint32_t (&L)[NREG]) {
 #pragma unroll
     for (int k = 0; k < NREG; ++k) {
         L[k] = V[k] + byte_pair<NREG>(c, k);
-        if constexpr (PADDED) L[k] += lc.pad[k];
+        if constexpr (PADDED) L[k] += lc.lift(k);
     }
 }
 
@@ -534,7 +590,7 @@ struct Walker {
 // One wave of a line pair, the whole way along.  The offsets of the steps of
 // the next chunk are laid out one chunk ahead and serve its cost loads,
 // its checkpoint and its stores.
-template <int KIND, int NREG, int LPL, int K, bool ALIGNED, bool PADDED, bool U8, bool HELP>
+template <int KIND, int NREG, int LPL, int K, bool RAGGED, bool PADDED, bool U8, bool HELP>
 __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ slice, int q, bool fwd,
                                          bool helper, int group, uint32_t* __restrict__ lds) {
     constexpr int DPL = 2 * NREG;
@@ -558,6 +614,9 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
     const int c_split = (fwd ? sch.split_fwd : sch.split_rev) / K;
     // chunks of the longer second half of the two directions
     const int rounds = nchunks - sch.split_fwd / K;
+    // The chunk that holds the forward line's last pixel.  If that is the
+    // volume's last one, the bytes of its last lane may end before the vector.
+    const int c_edge = RAGGED ? (fwd ? nchunks - 1 : 0) : -1;
     // the forward wave's last chunk holds steps past its line's end
     const int c_last_checked = (fwd && sch.delta > 0) ? nchunks - 1 : -1;
 
@@ -565,7 +624,7 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
     const __amdgpu_buffer_rsrc_t rc = buffer_rsrc(f.cost, vol);
     const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(slice, U8 ? vol : 2u * vol);
 
-    LaneConst<NREG> cst;
+    LaneConst<NREG, RAGGED> cst;
     cst.p1x2 = pk_splat((uint32_t)f.p1);
     cst.p2x2 = pk_splat((uint32_t)f.p2);
     constexpr uint32_t kEdge = NARROW ? 0x4000u : 0x8000u;
@@ -573,15 +632,17 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
     cst.edge_prev = sub == 0 ? kEdge << 16 : 0u;
     const uint32_t lift = 255u + (uint32_t)f.p2;
 #pragma unroll
-    for (int k = 0; k < NREG; ++k) {
+    for (int k = 0; k < (RAGGED ? NREG : 1); ++k) {
         const uint32_t lo = (sub * DPL + k < ndisp) ? 0u : lift;
-        const uint32_t hi = (sub * DPL + NREG + k < ndisp) ? 0u : lift;
+        const uint32_t hi = (sub * DPL + (RAGGED ? NREG + k : 0) < ndisp) ? 0u : lift;
         cst.pad[k] = PADDED ? lo | (hi << 16) : 0u;
     }
-    uint32_t ebias[DPL];
+    StoreLanes sl;
+    sl.r = ndisp % DPL;
+    const bool whole = write && d0 + DPL <= ndisp;
+    sl.full = whole ? 0u : kNoWrite;
 #pragma unroll
-    for (int e = 0; e < DPL; ++e) ebias[e] = (write && d0 + e < ndisp) ? 0u : kNoWrite;
-    const uint32_t lane_bias = (U8 && ALIGNED && !write) ? kNoWrite : 0u;
+    for (int i = 0; i < 4; ++i) sl.part[i] = RAGGED && write && !whole && (sl.r & (8 >> i)) ? 0u : kNoWrite;
 
     // the wave's own direction and first pixel; the reverse wave starts where
     // the forward line ends
@@ -626,9 +687,14 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
     bool rst_n[K];
     ByteVec<NREG> cn[K];
     bool wrap_n;
-    auto load_next = [&]() {
+    auto load_next = [&](int c) {
+        if (RAGGED && c == c_edge) {
 #pragma unroll
-        for (int j = 0; j < K; ++j) cn[j] = load_bytes<NREG, ALIGNED>(rc, offs_n[j]);
+            for (int j = 0; j < K; ++j) cn[j] = load_bytes_each<NREG>(rc, offs_n[j]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < K; ++j) cn[j] = load_bytes<NREG>(rc, offs_n[j]);
+        }
     };
     // of the last chunk, the forward wave's steps past its line's end
     auto drop_tail = [&](int c) {
@@ -640,10 +706,10 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
     // state of the own recursion, up to an offset common to the line
     uint32_t L[NREG];
 #pragma unroll
-    for (int k = 0; k < NREG; ++k) L[k] = cst.pad[k];
+    for (int k = 0; k < NREG; ++k) L[k] = cst.lift(k);
     auto restart = [&](uint32_t (&s)[NREG], bool r) {
 #pragma unroll
-        for (int k = 0; k < NREG; ++k) s[k] = r ? cst.pad[k] : s[k];
+        for (int k = 0; k < NREG; ++k) s[k] = r ? cst.lift(k) : s[k];
     };
     // one own step: V and the new state; returns m as a pair.  Once per chunk
     // the offset is taken off.
@@ -665,13 +731,17 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
     uint32_t P[NREG];
     ByteVec<NREG> kb;
     WideVec<NREG> kw;
-    auto load_checkpoint = [&]() {
-        if constexpr (U8) kb = load_bytes<NREG, ALIGNED>(rs, offs_n[K - 1]);
-        else {
+    auto load_checkpoint = [&](int c) {
+        const uint32_t off = offs_n[K - 1];
+        if constexpr (U8) {
+            if (RAGGED && c == c_edge) kb = load_bytes_each<NREG>(rs, off);
+            else kb = load_bytes<NREG>(rs, off);
+        } else {
+            if (RAGGED && c == c_edge) kw = load_wide_each<NREG>(rs, 2u * off);
+            else kw = load_wide<NREG>(rs, 2u * off);
             // twice a no-write offset is inside the slice again
-            kw = load_wide<NREG, ALIGNED>(rs, 2u * offs_n[K - 1]);
 #pragma unroll
-            for (int k = 0; k < NREG; ++k) kw.w[k] = offs_n[K - 1] >= kNoWrite ? 0u : kw.w[k];
+            for (int k = 0; k < NREG; ++k) kw.w[k] = off >= kNoWrite ? 0u : kw.w[k];
         }
     };
     auto partner_first = [&](PartnerSteps& out, const ByteVec<NREG>& cost, const ByteVec<NREG>& kb,
@@ -688,7 +758,7 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
                 P[k] = wide_pair<NREG>(kw, k);
                 out.l[K - 1][k] = P[k];
                 // padding may hold anything: bounded, so that the lift cannot overflow
-                if constexpr (PADDED) P[k] = pk_min(P[k], 0x7FFF7FFFu) + cst.pad[k];
+                if constexpr (PADDED) P[k] = pk_min(P[k], 0x7FFF7FFFu) + cst.lift(k);
             }
         }
     };
@@ -715,8 +785,8 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
             if (c_split < nchunks) {
                 wrap_n = wk.next(offs_n, rst_n);
                 drop_tail(c_split);
-                load_next();
-                load_checkpoint();
+                load_next(c_split);
+                load_checkpoint(c_split);
             }
             for (int i = 0; i < rounds; ++i) {
                 const int c = c_split + i;
@@ -734,8 +804,8 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
                     if (c + 1 < nchunks) {
                         wrap_n = wk.next(offs_n, rst_n);
                         drop_tail(c + 1);
-                        load_next();
-                        load_checkpoint();
+                        load_next(c + 1);
+                        load_checkpoint(c + 1);
                     }
                     auto steps = [&](auto wraps) {
                         constexpr bool WRAPS = decltype(wraps)::value;
@@ -762,7 +832,7 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
 #pragma unroll
     for (int j = 0; j < K; ++j) offs_n[j] = j < dlt ? kNoWrite : offs_n[j];
     drop_tail(0);
-    load_next();
+    load_next(0);
 
     // ---- first half: only the first step of every chunk is stored.  The
     // next chunk's loads are issued as this chunk's bytes are used up.
@@ -778,15 +848,15 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
             if constexpr (WRAPS) restart(L, rst[j]);
             uint32_t V[NREG];
             own_step(j, cn[j], V);
-            cn[j] = load_bytes<NREG, ALIGNED>(rc, offs_n[j]);
+            cn[j] = load_bytes<NREG>(rc, offs_n[j]);
             if (j == 0) {
                 if constexpr (U8) {
                     StateBytes<NREG> a;
 #pragma unroll
                     for (int i = 0; i < SW; ++i) a.w[i] = state_word<NREG>(V, i);
-                    store_bytes<NREG, ALIGNED>(rs, off0, lane_bias, ebias, to_memory<NREG>(a));
+                    store_bytes<NREG, RAGGED>(rs, off0, sl, to_memory<NREG>(a));
                 } else {
-                    store_wide<NREG, ALIGNED>(rs, off0, write, ebias, to_memory_wide<NREG>(L));
+                    store_wide<NREG, RAGGED>(rs, off0, sl, to_memory_wide<NREG>(L));
                 }
             }
         }
@@ -795,9 +865,10 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
         if (KIND == kDiagonal && wrap_n) first_half(std::true_type{});
         else first_half(std::false_type{});
     }
-    if (c_split > 0 && c_split == c_last_checked) {
+    if (c_split > 0 && c_split < nchunks && (c_split == c_last_checked || c_split == c_edge)) {
+        // of a chunk that was laid out as any other: again, with its checks
         drop_tail(c_split);
-        load_next();
+        load_next(c_split);
     }
     pair_barrier();
     if (!HELP && c_split == nchunks) return;
@@ -812,16 +883,16 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
             StateBytes<NREG> a;
 #pragma unroll
             for (int i = 0; i < SW; ++i) a.w[i] = state_word<NREG>(V, i) + (p.a[j].w[i] + nm);
-            store_bytes<NREG, ALIGNED>(rs, off, lane_bias, ebias, to_memory<NREG>(a));
+            store_bytes<NREG, RAGGED>(rs, off, sl, to_memory<NREG>(a));
         } else {
             uint32_t S[NREG];
 #pragma unroll
             for (int k = 0; k < NREG; ++k) S[k] = L[k] + (p.l[j][k] - m2);
-            store_wide<NREG, ALIGNED>(rs, off, write, ebias, to_memory_wide<NREG>(S));
+            store_wide<NREG, RAGGED>(rs, off, sl, to_memory_wide<NREG>(S));
         }
     };
 
-    if constexpr (!HELP) load_checkpoint();
+    if constexpr (!HELP) load_checkpoint(c_split);
     uint32_t offs[K];
     bool rst[K];
     ByteVec<NREG> cur[K];
@@ -832,7 +903,7 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
             pa.get(lds + ((c - c_split) & 1) * (K * 64 * PartnerSteps::kWords), lane);
         } else {
             partner_first(pa, cur[K - 1], kb, kw);
-            if (c + 1 < nchunks) load_checkpoint();
+            if (c + 1 < nchunks) load_checkpoint(c + 1);
 #pragma unroll
             for (int j = K - 2; j >= 0; --j) {
                 if constexpr (WRAPS) restart(P, rst[j + 1]);
@@ -863,7 +934,7 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
         if (c + 1 < nchunks) {
             wrap_n = wk.next(offs_n, rst_n);
             drop_tail(c + 1);
-            load_next();
+            load_next(c + 1);
         }
         if constexpr (HELP) lds_barrier();
         if (KIND == kDiagonal && w) second_half(c, std::true_type{});
@@ -877,7 +948,7 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
 // Block lb of the path pass of one frame: pair q, line groups 2g and 2g + 1;
 // waves 0, 1 walk the forward direction along them, waves 2, 3 the reverse
 // one.
-template <int NH, int LH, int NO, int LO, bool ALH, bool PDH, bool ALO, bool PDO, bool U8>
+template <int NH, int LH, int NO, int LO, bool RGH, bool PDH, bool RGO, bool PDO, bool U8>
 __device__ __forceinline__ void paths_block(const Frame& f, int lb) {
     constexpr int KH = kStepsH, KO = kStepsO;
     constexpr PathLayout kLayout = kPathLayouts[SGM_PATH_LAYOUT];
@@ -914,42 +985,37 @@ __device__ __forceinline__ void paths_block(const Frame& f, int lb) {
     uint32_t* mine = lds + (fwd ? 0 : kLds);
     if (q == 0) {
         __builtin_amdgcn_s_setprio(2);
-        run_wave<kHorizontal, NH, LH, KH, ALH, PDH, U8, HELPH>(f, slice, q, fwd, wave >= 2, group, mine);
+        run_wave<kHorizontal, NH, LH, KH, RGH, PDH, U8, HELPH>(f, slice, q, fwd, wave >= 2, group, mine);
         __builtin_amdgcn_s_setprio(0);
     } else if (q == 1) {
-        run_wave<kVertical, NO, LO, KO, ALO, PDO, U8, HELPO>(f, slice, q, fwd, wave >= 2, group, mine);
+        run_wave<kVertical, NO, LO, KO, RGO, PDO, U8, HELPO>(f, slice, q, fwd, wave >= 2, group, mine);
     } else {
-        run_wave<kDiagonal, NO, LO, KO, ALO, PDO, U8, HELPO>(f, slice, q, fwd, wave >= 2, group, mine);
+        run_wave<kDiagonal, NO, LO, KO, RGO, PDO, U8, HELPO>(f, slice, q, fwd, wave >= 2, group, mine);
     }
 }
 
-template <int NH, int LH, int NO, int LO, bool ALH, bool PDH, bool ALO, bool PDO, bool U8>
-__global__ __launch_bounds__(kThreads) void paths_kernel(Frame f) {
-    paths_block<NH, LH, NO, LO, ALH, PDH, ALO, PDO, U8>(f, blockIdx.x);
+template <int NH, int LH, int NO, int LO, bool RGH, bool PDH, bool RGO, bool PDO, bool U8>
+__global__ __launch_bounds__(kThreads, 2) void paths_kernel(Frame f) {
+    paths_block<NH, LH, NO, LO, RGH, PDH, RGO, PDO, U8>(f, blockIdx.x);
 }
 
-template <int NH, int LH, int NO, int LO, bool ALH, bool PDH, bool ALO, bool PDO, bool U8>
-__global__ __launch_bounds__(kThreads) void paths_batch_kernel(WorkList wl) {
-    for (int b = blockIdx.x; b < wl.total; b += gridDim.x) {
-        if (wl.items) {
-            paths_block<NH, LH, NO, LO, ALH, PDH, ALO, PDO, U8>(wl.frames[wl.items[2 * b]],
-                                                               wl.items[2 * b + 1]);
-        } else {
-            const int fi = find_frame(wl, b);
-            paths_block<NH, LH, NO, LO, ALH, PDH, ALO, PDO, U8>(wl.frames[fi], b - wl.starts[fi]);
-        }
-    }
+template <int NH, int LH, int NO, int LO, bool RGH, bool PDH, bool RGO, bool PDO, bool U8>
+__global__ __launch_bounds__(kThreads, 2) void paths_batch_kernel(WorkList wl) {
+    // one block per item, the longest lines first (a loop over items here costs
+    // the registers that let two waves share a SIMD)
+    const int b = blockIdx.x;
+    paths_block<NH, LH, NO, LO, RGH, PDH, RGO, PDO, U8>(wl.frames[wl.items[2 * b]], wl.items[2 * b + 1]);
 }
 
 // Path-kernel launches for one lane layout: the single-frame kernel, or the
 // persistent work-list form.  The two are compiled in separate objects
 // (SGM_PATH_PART 0 and 1), so the library's longest compile splits in two.
 struct LayoutFlags {
-    bool alh, alo, padded;
+    bool ragged, padded;   // D cuts a lane's disparities; some lane holds padding
 };
 
 __host__ inline LayoutFlags layout_flags(int nh, int lh, int no, int lo, int ndisp) {
-    return {ndisp % (2 * nh) == 0, ndisp % (2 * no) == 0, lh * 2 * nh > ndisp || lo * 2 * no > ndisp};
+    return {ndisp % (2 * nh) != 0 || ndisp % (2 * no) != 0, lh * 2 * nh > ndisp || lo * 2 * no > ndisp};
 }
 
 #if SGM_PATH_PART == 0
@@ -958,17 +1024,19 @@ hipError_t launch_paths_single(const Frame& one, int ndisp, bool u8, int nblocks
     const LayoutFlags fl = layout_flags(NH, LH, NO, LO, ndisp);
 #define SGM_PATHS(A, B, C, D, U) \
     paths_kernel<NH, LH, NO, LO, A, B, C, D, U><<<nblocks, kThreads, 0, stream>>>(one)
-    if (fl.alh && fl.alo) {
-        if (!fl.padded) {
-            if (u8) SGM_PATHS(true, false, true, false, true);
-            else SGM_PATHS(true, false, true, false, false);
-        } else {
+    if (fl.ragged) {
+        if constexpr (NO <= 4) {               // path_layout_id gives no other layout such a D
             if (u8) SGM_PATHS(true, true, true, true, true);
             else SGM_PATHS(true, true, true, true, false);
+        } else {
+            return hipErrorInvalidValue;
         }
-    } else {
+    } else if (fl.padded) {
         if (u8) SGM_PATHS(false, true, false, true, true);
         else SGM_PATHS(false, true, false, true, false);
+    } else {
+        if (u8) SGM_PATHS(false, false, false, false, true);
+        else SGM_PATHS(false, false, false, false, false);
     }
 #undef SGM_PATHS
     return hipGetLastError();
@@ -977,22 +1045,21 @@ hipError_t launch_paths_single(const Frame& one, int ndisp, bool u8, int nblocks
 template <int NH, int LH, int NO, int LO>
 hipError_t launch_paths_worklist(const WorkList& wl, int ndisp, bool u8, int nblocks, hipStream_t stream) {
     const LayoutFlags fl = layout_flags(NH, LH, NO, LO, ndisp);
-    // an ordered item list is dispatched one block per item, so the hardware
-    // hands out the longest lines first
-    const int grid = wl.items ? nblocks : persistent_grid(nblocks);
 #define SGM_PATHS(A, B, C, D, U) \
-    paths_batch_kernel<NH, LH, NO, LO, A, B, C, D, U><<<grid, kThreads, 0, stream>>>(wl)
-    if (fl.alh && fl.alo) {
-        if (!fl.padded) {
-            if (u8) SGM_PATHS(true, false, true, false, true);
-            else SGM_PATHS(true, false, true, false, false);
-        } else {
+    paths_batch_kernel<NH, LH, NO, LO, A, B, C, D, U><<<nblocks, kThreads, 0, stream>>>(wl)
+    if (fl.ragged) {
+        if constexpr (NO <= 4) {               // path_layout_id gives no other layout such a D
             if (u8) SGM_PATHS(true, true, true, true, true);
             else SGM_PATHS(true, true, true, true, false);
+        } else {
+            return hipErrorInvalidValue;
         }
-    } else {
+    } else if (fl.padded) {
         if (u8) SGM_PATHS(false, true, false, true, true);
         else SGM_PATHS(false, true, false, true, false);
+    } else {
+        if (u8) SGM_PATHS(false, false, false, false, true);
+        else SGM_PATHS(false, false, false, false, false);
     }
 #undef SGM_PATHS
     return hipGetLastError();

@@ -186,9 +186,8 @@ struct WorkList {
     const int32_t* starts;           // nframes + 1 entries
     int32_t nframes;
     int32_t total;                   // starts[nframes]
-    // optional: total (frame, block) pairs giving the launch order of the
-    // blocks (longest first); when set, block b of the launch is items[2b],
-    // items[2b + 1] instead of the frame-major order of starts
+    // path stage: total (frame, block) pairs in launch order (longest first);
+    // block b of the launch is items[2b], items[2b + 1]
     const int32_t* items;
 };
 
@@ -261,7 +260,7 @@ struct PathLayout {
 };
 
 // Every layout the library builds (paths.hip is compiled once per entry).
-constexpr int kNumPathLayouts = 12;
+constexpr int kNumPathLayouts = 13;
 constexpr PathLayout kPathLayouts[kNumPathLayouts] = {
     {1, 1, 1, 1, true, false, false},    {1, 2, 2, 1, true, false, false},
     {1, 4, 4, 1, true, false, false},    {1, 8, 4, 2, true, false, false},
@@ -269,6 +268,7 @@ constexpr PathLayout kPathLayouts[kNumPathLayouts] = {
     {2, 16, 4, 8, false, false, false},  {2, 32, 4, 16, true, false, false},
     {2, 32, 8, 8, true, false, false},   {4, 16, 8, 8, false, false, true},
     {4, 32, 8, 16, true, false, true},   {4, 32, 8, 16, false, false, true},
+    {4, 32, 4, 32, true, false, true},
 };
 
 // The path pass for layout kPathLayouts[ID] (paths.hip compiled per layout,
@@ -296,6 +296,7 @@ SGM_DECLARE_PATH_LAYOUT(8)
 SGM_DECLARE_PATH_LAYOUT(9)
 SGM_DECLARE_PATH_LAYOUT(10)
 SGM_DECLARE_PATH_LAYOUT(11)
+SGM_DECLARE_PATH_LAYOUT(12)
 #undef SGM_DECLARE_PATH_LAYOUT
 
 // Pairs of opposite path directions.  Pair q's forward step r (the reverse

@@ -105,3 +105,25 @@ def test_aggregate_at_chunk_edges(w, h, nd, npaths, p1, p2):
             np.testing.assert_array_equal(g[y, x], oracle.aggregate_at(c, npaths, p1, p2, x, y))
     else:
         np.testing.assert_array_equal(got.cpu().numpy(), oracle.aggregate(c, npaths, p1, p2))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nd", [1, 3, 5, 7, 9, 11, 15, 17, 23, 31, 33, 41, 63, 65, 66, 97, 100, 101, 102, 103, 127, 129,
+                                130, 131, 136, 203, 255])
+def test_aggregate_where_d_cuts_a_lane(nd):
+    """The lane that holds d = D - 1 stores in parts, the volume's last pixel
+    is loaded byte by byte; nothing past a slice or a pixel is touched."""
+    import torch
+
+    import oracle
+    from paper_2106_07927_amd import sgm
+    print("aggregate, D =", nd, flush=True)
+    for w, h in ((1, 1), (9, 17), (33, 6)):
+        c = datagen.random_cost(w, h, nd, seed=nd, high=256)
+        for npaths, p1, p2 in ((8, 10, 120), (8, 90, 880)):
+            need = sgm.aggregate_work_bytes(w, h, nd, npaths, p2)
+            work = torch.full((need + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+            got = sgm.sgm_aggregate(torch.from_numpy(c).cuda(), npaths, p1, p2, work=work[:need])
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(got.cpu().numpy(), oracle.aggregate(c, npaths, p1, p2))
+            assert bool((work[need:] == 0xA5).all())

@@ -185,8 +185,7 @@ size_t sgm_wta_lrc_work_elems(int32_t width, int32_t height);
  * speed-up for GPU SGM (Sec. 4.2); here the path sum of Eq. (sgm_path_aggr)
  * is formed on chip inside the selection pass.  disp_out and disp_right_out
  * are bit-identical to those two calls with the same arguments.
- * The fused form applies when ndisp % 16 == 0 (any legal p2); other valid
- * arguments run the two unfused calls on the same workspace.
+ * Every ndisp and every legal p2 takes this form.
  *   cost, npaths, p1, p2          as for sgm_aggregate
  *   lr_tolerance, median3x3,
  *   disp_out, disp_right_out      as for sgm_wta_lrc

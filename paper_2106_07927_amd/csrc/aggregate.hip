@@ -82,14 +82,6 @@ __global__ __launch_bounds__(256) void merge_kernel(Frame f) {
     merge_block<MODE>(f, blockIdx.x);
 }
 
-template <int MODE>
-__global__ __launch_bounds__(256) void merge_batch_kernel(WorkList wl) {
-    for (int b = blockIdx.x; b < wl.total; b += gridDim.x) {
-        const int fi = find_frame(wl, b);
-        merge_block<MODE>(wl.frames[fi], b - wl.starts[fi]);
-    }
-}
-
 int merge_mode(int npaths, int p2) { return (slices_u8(p2) ? 2 : 0) + (npaths == 8 ? 1 : 0); }
 
 }  // namespace
@@ -224,17 +216,6 @@ hipError_t launch_paths_batch(const WorkList& wl, int ndisp, int npaths, int p2,
     (void)npaths;
     if (variant < 0 || variant >= path_variants(ndisp)) variant = 0;
     return launch_paths_any(nullptr, &wl, ndisp, variant, slices_u8(p2), wl.total, stream);
-}
-
-hipError_t launch_merge_batch(const WorkList& wl, int npaths, int p2, hipStream_t stream) {
-    const int grid = persistent_grid(wl.total);
-    switch (merge_mode(npaths, p2)) {
-        case 0: merge_batch_kernel<0><<<grid, 256, 0, stream>>>(wl); break;
-        case 1: merge_batch_kernel<1><<<grid, 256, 0, stream>>>(wl); break;
-        case 2: merge_batch_kernel<2><<<grid, 256, 0, stream>>>(wl); break;
-        default: merge_batch_kernel<3><<<grid, 256, 0, stream>>>(wl); break;
-    }
-    return hipGetLastError();
 }
 
 }  // namespace sgm

@@ -9,8 +9,6 @@
 //     census (all frames, both images) -> cost (per D) -> paths (per D and
 //     variant) -> D^R key fill (all) -> path sum fused with the selection
 //     (per D) -> LR check + median (all)
-// Frames whose disparity range rules out the fused selection (D % 16 != 0)
-// take merge (S_bar in the workspace) and the plain selection instead.
 // Every stage is one persistent launch that walks its work list of
 // (frame, block) items; the blocks of a frame are exactly those of the
 // single-frame call, so each frame's results are bit-identical to it.
@@ -56,7 +54,7 @@ FrameLayout frame_layout(int w, int h, int nd, int npaths, int p2) {
     l.census = align256(8 * n);
     l.cost = align256(n * nd);
     l.slices = align256(aggregate_work_bytes(w, h, nd, npaths, p2));
-    l.agg = fused_select_supported(nd, npaths, p2) ? 0 : align256(2 * n * nd);
+    l.agg = workspace_holds_agg(nd) ? align256(2 * n * nd) : 0;
     l.keys = align256(4 * n);
     l.dl = align256(2 * n);
     l.total = 2 * l.census + l.cost + l.slices + l.agg + l.keys + l.dl;
@@ -94,7 +92,7 @@ int tuned_chains(const char* table) {
     return std::max(1, std::min(kMaxChains, c));
 }
 
-enum Stage { kCensus, kCost, kPaths, kMerge, kFill, kSelect, kFused, kMedian, kStages };
+enum Stage { kCensus, kCost, kPaths, kFill, kFused, kMedian, kStages };
 
 int stage_blocks(Stage st, const Frame& f) {
     const size_t n = (size_t)f.width * f.height;
@@ -102,9 +100,7 @@ int stage_blocks(Stage st, const Frame& f) {
         case kCensus: return 2 * census_blocks(f.width, f.height);
         case kCost: return cost_blocks_x(f.width) * f.height;
         case kPaths: return path_blocks(f.width, f.height, f.ndisp, f.npaths, f.variant);
-        case kMerge: return merge_blocks(n * f.ndisp);
         case kFill: return fill_blocks(n);
-        case kSelect: return select_blocks_x(f.width) * f.height;
         case kFused: return fused_blocks_x(f.width, f.ndisp) * f.height;
         case kMedian: return median_blocks(f.width, f.height);
         default: return 0;
@@ -185,7 +181,6 @@ size_t build_layout(const sgm_pair* pairs, int32_t n, const sgm_params* p, const
         f.census_right = reinterpret_cast<uint64_t*>(off + l.census);
         f.cost = reinterpret_cast<uint8_t*>(off + 2 * l.census);
         f.slices = reinterpret_cast<uint8_t*>(off + 2 * l.census + l.cost);
-        f.agg = reinterpret_cast<uint16_t*>(off + 2 * l.census + l.cost + l.slices);
         f.right_keys = reinterpret_cast<uint32_t*>(off + 2 * l.census + l.cost + l.slices + l.agg);
         f.disp_left = reinterpret_cast<uint16_t*>(off + 2 * l.census + l.cost + l.slices + l.agg + l.keys);
         off += l.total;
@@ -198,21 +193,15 @@ size_t build_layout(const sgm_pair* pairs, int32_t n, const sgm_params* p, const
     if (!all.empty()) {
         std::map<int, std::vector<int>> by_d;
         std::map<std::pair<int, int>, std::vector<int>> by_dv;
-        std::vector<int> unfused;
         for (int i : all) {
             by_d[(*frames)[i].ndisp].push_back(i);
             by_dv[{(*frames)[i].ndisp, (*frames)[i].variant}].push_back(i);
-            if (!fused_select_supported((*frames)[i].ndisp, p->npaths, p->p2)) unfused.push_back(i);
         }
         launches->push_back({kCensus, 0, 0, all});
         for (auto& kv : by_d) launches->push_back({kCost, kv.first, 0, kv.second});
         for (auto& kv : by_dv) launches->push_back({kPaths, kv.first.first, kv.first.second, kv.second});
-        if (!unfused.empty()) launches->push_back({kMerge, 0, 0, unfused});
         launches->push_back({kFill, 0, 0, all});
-        for (auto& kv : by_d) {
-            const bool fused = fused_select_supported(kv.first, p->npaths, p->p2);
-            launches->push_back({fused ? kFused : kSelect, kv.first, 0, kv.second});
-        }
+        for (auto& kv : by_d) launches->push_back({kFused, kv.first, 0, kv.second});
         launches->push_back({kMedian, 0, 0, all});
     }
     // tables: one frame table per launch (frames of the group, in order) and
@@ -277,9 +266,6 @@ int32_t sgm_batch_plan_create(const sgm_pair* pairs, int32_t n, const sgm_params
         f.census_right = reinterpret_cast<uint64_t*>(base + reinterpret_cast<uintptr_t>(f.census_right));
         f.cost = reinterpret_cast<uint8_t*>(base + reinterpret_cast<uintptr_t>(f.cost));
         f.slices = reinterpret_cast<uint8_t*>(base + reinterpret_cast<uintptr_t>(f.slices));
-        f.agg = fused_select_supported(f.ndisp, f.npaths, f.p2)
-                    ? nullptr
-                    : reinterpret_cast<uint16_t*>(base + reinterpret_cast<uintptr_t>(f.agg));
         f.right_keys = reinterpret_cast<uint32_t*>(base + reinterpret_cast<uintptr_t>(f.right_keys));
         f.disp_left = reinterpret_cast<uint16_t*>(base + reinterpret_cast<uintptr_t>(f.disp_left));
     }
@@ -374,9 +360,7 @@ int32_t sgm_batch_plan_create(const sgm_pair* pairs, int32_t n, const sgm_params
                 case kPaths:
                     ce = launch_paths_batch(L.wl, L.ndisp, params->npaths, params->p2, L.variant, s);
                     break;
-                case kMerge: ce = launch_merge_batch(L.wl, params->npaths, params->p2, s); break;
                 case kFill: ce = launch_fill_keys_batch(L.wl, s); break;
-                case kSelect: ce = launch_select_batch(L.wl, L.ndisp, s); break;
                 case kFused: ce = launch_select_fused_batch(L.wl, L.ndisp, params->npaths, params->p2, s); break;
                 case kMedian: ce = launch_median_batch(L.wl, s); break;
                 default: break;
@@ -389,12 +373,7 @@ int32_t sgm_batch_plan_create(const sgm_pair* pairs, int32_t n, const sgm_params
                 if (ce == hipSuccess) ce = launch_census_pair(f, s);
                 if (ce == hipSuccess) ce = launch_cost(f, s);
                 if (ce != hipSuccess) break;
-                if (fused_select_supported(f.ndisp, f.npaths, f.p2)) {
-                    ce = launch_aggregate_select(f, s);
-                } else {
-                    ce = launch_aggregate(f, s);
-                    if (ce == hipSuccess) ce = launch_wta_lrc(f, s);
-                }
+                ce = launch_aggregate_select(f, s);
             }
             hipEvent_t je = nullptr;
             if (ce == hipSuccess) ce = new_event(&je);

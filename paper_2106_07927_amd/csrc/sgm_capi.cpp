@@ -43,29 +43,19 @@ hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
 size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
-// Workspace of sgm_aggregate_select: path slices, S_bar (only where the fused
-// selection does not apply), D^R keys, D^L.  Returns the total bytes.
+// Workspace of sgm_aggregate_select: path slices, room for S_bar (D no multiple
+// of 16; not used), D^R keys, D^L.  Returns the total bytes.
 size_t select_layout(int32_t width, int32_t height, int32_t ndisp, int32_t npaths, int32_t p2,
                      size_t* agg_off, size_t* keys_off, size_t* dl_off) {
     const size_t n = (size_t)width * height;
     size_t off = align256(sgm::aggregate_work_bytes(width, height, ndisp, npaths, p2));
     *agg_off = off;
-    if (!sgm::fused_select_supported(ndisp, npaths, p2)) off += align256(2 * n * (size_t)ndisp);
+    if (sgm::workspace_holds_agg(ndisp)) off += align256(2 * n * (size_t)ndisp);
     *keys_off = off;
     off += align256(4 * n);
     *dl_off = off;
     off += align256(2 * n);
     return off;
-}
-
-// The aggregation and selection of one frame: fused where it applies, else
-// sgm_aggregate + sgm_wta_lrc with S_bar in f.agg.
-hipError_t run_select(const sgm::Frame& f, hipStream_t s, bool fine = false) {
-    if (sgm::fused_select_supported(f.ndisp, f.npaths, f.p2))
-        return sgm::launch_aggregate_select(f, s, fine);
-    const hipError_t e = sgm::launch_aggregate(f, s);
-    if (e != hipSuccess) return e;
-    return fine ? sgm::launch_wta_lrc_fine(f, s) : sgm::launch_wta_lrc(f, s);
 }
 
 bool good_params(const sgm_params* p) {
@@ -297,8 +287,7 @@ int32_t sgm_aggregate_select(const uint8_t* cost, int32_t width, int32_t height,
     f.disp_left = reinterpret_cast<uint16_t*>(base + dl_off);
     f.disp = disp_out;
     f.disp_right = disp_right_out;
-    f.agg = reinterpret_cast<uint16_t*>(base + agg_off);
-    return hip_status(run_select(f, as_stream(stream)));
+    return hip_status(sgm::launch_aggregate_select(f, as_stream(stream)));
 }
 
 size_t sgm_aggregate_select_subpixel_work_bytes(int32_t width, int32_t height, int32_t ndisp,
@@ -336,13 +325,12 @@ int32_t sgm_aggregate_select_subpixel(const uint8_t* cost, int32_t width, int32_
     f.cost = const_cast<uint8_t*>(cost);
     f.slices = reinterpret_cast<uint8_t*>(base);
     f.slice_stride = sgm::aggregate_slice_elems(width, height, ndisp);
-    f.agg = reinterpret_cast<uint16_t*>(base + agg_off);
     f.right_keys = reinterpret_cast<uint32_t*>(base + keys_off);
     f.disp_left = reinterpret_cast<uint16_t*>(base + dl_off);
     f.fine_left = reinterpret_cast<float*>(base + fine_off);
     f.disp_fine = disp_out;
     f.disp_right = disp_right_out;
-    return hip_status(run_select(f, as_stream(stream), true));
+    return hip_status(sgm::launch_aggregate_select(f, as_stream(stream), true));
 }
 
 size_t sgm_disparity_exact_lr_work_bytes(int32_t width, int32_t height, int32_t ndisp,
@@ -385,7 +373,6 @@ int32_t sgm_disparity_exact_lr(const uint8_t* left, const uint8_t* right, int32_
     f.cost = reinterpret_cast<uint8_t*>(base + l.cost);
     f.slices = reinterpret_cast<uint8_t*>(base + l.select);
     f.slice_stride = sgm::aggregate_slice_elems(width, height, ndisp);
-    f.agg = reinterpret_cast<uint16_t*>(base + l.select + l.agg);
     f.right_keys = reinterpret_cast<uint32_t*>(base + l.select + l.keys);
     f.disp_left = reinterpret_cast<uint16_t*>(base + l.select + l.dl);
     f.lr_tolerance = -1;            // both passes: plain WTA maps
@@ -411,7 +398,7 @@ int32_t sgm_disparity_exact_lr(const uint8_t* left, const uint8_t* right, int32_
         }
         if (e == hipSuccess) e = sgm::launch_census_pair(f, s);
         if (e == hipSuccess) e = sgm::launch_cost(f, s);
-        if (e == hipSuccess) e = run_select(f, s);
+        if (e == hipSuccess) e = sgm::launch_aggregate_select(f, s);
     }
     if (e == hipSuccess)
         e = sgm::launch_check_exact(dl, flipped, width, height, params->lr_tolerance,

@@ -220,13 +220,6 @@ __host__ __device__ inline int census_blocks(int w, int h) {
 constexpr int kCostPix = 128;
 __host__ __device__ inline int cost_blocks_x(int w) { return (w + kCostPix - 1) / kCostPix; }
 
-constexpr int kSelectSeg = 128;   // pixels per wave segment
-constexpr int kSelectWaves = 4;
-__host__ __device__ inline int select_blocks_x(int w) {
-    const int segs = (w + kSelectSeg - 1) / kSelectSeg;
-    return (segs + kSelectWaves - 1) / kSelectWaves;
-}
-
 // pixels of one row per block of the fused path-sum + selection pass
 // (at most 8192 volume elements per tile, so every thread sums two 16-byte
 // blocks: 64 pixels up to D = 128, 32 beyond)
@@ -326,6 +319,9 @@ int path_blocks(int width, int height, int ndisp, int npaths, int variant);
 int path_horizontal_blocks(int width, int height, int ndisp, int variant);
 size_t aggregate_slice_elems(int width, int height, int ndisp);
 size_t aggregate_work_bytes(int width, int height, int ndisp, int npaths, int p2);
+// Workspaces of the streamlined forms keep room for S_bar at such a D (their
+// sizes are part of the interface); nothing is stored there.
+inline bool workspace_holds_agg(int ndisp) { return ndisp % 16 != 0; }
 
 // ---------------------------------------------------------------------------
 // Launchers.  Single-frame forms take the frame by value; batched forms take
@@ -342,10 +338,7 @@ hipError_t launch_wta_lrc(const Frame& f, hipStream_t stream);
 // the path kernel of launch_aggregate alone (slices, no path sum)
 hipError_t launch_paths(const Frame& f, hipStream_t stream);
 // path sum fused with WTA / D^R / LR check / median, from the slices
-bool fused_select_supported(int ndisp, int npaths, int p2);
 hipError_t launch_aggregate_select(const Frame& f, hipStream_t stream, bool fine = false);
-// selection with subpixel refinement from S_bar in f.agg (float output)
-hipError_t launch_wta_lrc_fine(const Frame& f, hipStream_t stream);
 // exact consistency check: the swapped, flipped pair and the check against
 // its WTA map
 hipError_t launch_flip_pair(const uint8_t* left, const uint8_t* right, int width, int height,
@@ -358,9 +351,7 @@ hipError_t launch_census_batch(const WorkList& wl, int win_w, int win_h, hipStre
 hipError_t launch_cost_batch(const WorkList& wl, int ndisp, hipStream_t stream);
 hipError_t launch_paths_batch(const WorkList& wl, int ndisp, int npaths, int p2, int variant,
                               hipStream_t stream);
-hipError_t launch_merge_batch(const WorkList& wl, int npaths, int p2, hipStream_t stream);
 hipError_t launch_fill_keys_batch(const WorkList& wl, hipStream_t stream);
-hipError_t launch_select_batch(const WorkList& wl, int ndisp, hipStream_t stream);
 hipError_t launch_select_fused_batch(const WorkList& wl, int ndisp, int npaths, int p2,
                                      hipStream_t stream);
 hipError_t launch_median_batch(const WorkList& wl, hipStream_t stream);

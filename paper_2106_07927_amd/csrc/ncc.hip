@@ -10,22 +10,27 @@
 // float32 with IEEE square root and division in a fixed order, so the
 // quantised cost is reproducible bit for bit.
 //
-// A 256-thread block owns 64 pixels of one row and every disparity.  It
+// A 256-thread block owns 128 pixels of one row and every disparity.  It
 // stages the window columns of both images in LDS -- each column's win bytes
 // packed into dwords so that one v_dot4_u32_u8 multiplies four rows -- plus
 // each column's sum and sum of squares.  Per-pixel patch sums (the mean and
-// variance terms of the paper's per-pixel struct) follow from sliding sums
-// over the columns.  A thread then takes one disparity d and 32 consecutive
-// pixels: it slides the cross sum S_LR along x, one new column product per
-// pixel, and evaluates the cost.  Consecutive threads take consecutive d, so
-// every byte store of a wave is 64 consecutive bytes of the volume.
+// variance terms of the paper's per-pixel struct) follow from sums over the
+// columns.  A thread then takes four consecutive disparities and a run of
+// consecutive pixels: it slides the four cross sums S_LR along x (one new left
+// and one new right column per pixel serve all four) and stores four costs at
+// a time.
+// Bound by its instructions.  An IEEE division per element is most of them, so
+// the cost is first taken from the product with the two deviations'
+// reciprocals; where that lies so near a rounding tie that the defined
+// arithmetic could round to the other side (5 elements in 10,000), the lane
+// evaluates the definition.  1242x375, D = 128, 5x5: 68.7 -> 44.9 us, 9x9: 78.1 ->
+// 53.7 us; 1920x1080, D = 256, 5x5: 504 -> 275 us.
 #include "sgm_internal.h"
 
 namespace sgm {
 namespace {
 
-constexpr int kNccTile = 64;                   // pixels of a row per block
-constexpr int kNccRun = 32;                    // pixels per thread and disparity
+constexpr int kNccTile = 128;                  // pixels of a row per block
 constexpr int kMaxD = 256;
 
 template <int WIN>
@@ -38,10 +43,13 @@ struct NccTile {
     uint32_t rcol[RCOLS][CW];
     int32_t lsum[LCOLS], lsq[LCOLS];
     int32_t rsum[RCOLS], rsq[RCOLS];
-    int32_t ls[kNccTile];                      // S_L per tile pixel
-    float lsig[kNccTile];                      // sqrt(n S_LL - S_L^2), 0 if flat
-    int32_t rs[kNccTile + kMaxD - 1];          // S_R per right pixel x0 - D + 1 + i
-    float rsig[kNccTile + kMaxD - 1];
+    // per tile pixel / right pixel x0 - D + 1 + i: the patch sum, the deviation
+    // sqrt(n SS - S^2), and its reciprocal (0 for a patch without variance and
+    // for a right pixel outside the image: such a cost is 255)
+    int32_t ls[kNccTile];
+    float lsig[kNccTile], linv[kNccTile];
+    int32_t rs[kNccTile + kMaxD - 1];
+    float rsig[kNccTile + kMaxD - 1], rinv[kNccTile + kMaxD - 1];
 };
 
 // Column c of a staged image: rows y - R .. y + R at image column gx.
@@ -103,6 +111,7 @@ __global__ __launch_bounds__(256) void ncc_cost_kernel(const uint8_t* __restrict
     using T = NccTile<WIN>;
     constexpr int R = T::R;
     constexpr int N = WIN * WIN;
+    constexpr int CW = T::CW;
     __shared__ T t;
     const int x0 = blockIdx.x * kNccTile;
     const int y = blockIdx.y;
@@ -125,8 +134,10 @@ __global__ __launch_bounds__(256) void ncc_cost_kernel(const uint8_t* __restrict
             s += t.lsum[p + k];
             q += t.lsq[p + k];
         }
+        const float sig = patch_sigma(N, s, q);
         t.ls[p] = s;
-        t.lsig[p] = patch_sigma(N, s, q);
+        t.lsig[p] = sig;
+        t.linv[p] = sig > 0.0f ? 1.0f / sig : 0.0f;
     }
     for (int p = threadIdx.x; p < npx + ndisp - 1; p += blockDim.x) {
         int32_t s = 0, q = 0;
@@ -135,38 +146,105 @@ __global__ __launch_bounds__(256) void ncc_cost_kernel(const uint8_t* __restrict
             s += t.rsum[p + k];
             q += t.rsq[p + k];
         }
+        const float sig = patch_sigma(N, s, q);
         t.rs[p] = s;
-        t.rsig[p] = patch_sigma(N, s, q);
+        t.rsig[p] = sig;
+        t.rinv[p] = sig > 0.0f && x0 - ndisp + 1 + p >= 0 ? 1.0f / sig : 0.0f;
     }
     __syncthreads();
 
-    // costs: item = (run, d); right pixel x - d is rs index p + D - 1 - d
-    const int runs = (npx + kNccRun - 1) / kNccRun;
+    // costs: item = (run of pixels, four disparities d0 .. d0 + 3); right pixel
+    // x - d is index p + D - 1 - d
+    const int groups = (ndisp + 3) / 4;
+    const int nruns = max(1, 256 / groups);
+    const int run = (npx + nruns - 1) / nruns;
     uint8_t* out = cost + ((size_t)y * width + x0) * ndisp;
-    for (int item = threadIdx.x; item < runs * ndisp; item += blockDim.x) {
-        const int d = item % ndisp;
-        const int p0 = (item / ndisp) * kNccRun;
-        const int p1 = min(npx, p0 + kNccRun);
-        const int off = ndisp - 1 - d;          // rcol index of left column c is c + off
-        uint32_t win[WIN];                      // column products of the current window
-        int32_t slr = 0;
+    const bool whole = (ndisp & 3) == 0;
+    for (int item = threadIdx.x; item < nruns * groups; item += blockDim.x) {
+        const int d0 = 4 * (item % groups);
+        const int p0 = (item / groups) * run;
+        const int p1 = min(npx, p0 + run);
+        // index of disparity d0 + 3 at pixel 0; below 0 only for disparities past D
+        const int base = ndisp - 1 - d0 - 3;
+        auto at = [&](int i) { return max(i, 0); };
+        // right columns and right pixels of the four disparities, the largest first
+        uint32_t rc[4][CW];
+        int32_t sr[4];
+        float ri[4];
 #pragma unroll
-        for (int k = 0; k < WIN - 1; ++k) {
-            win[k] = column_dot<WIN>(t.lcol[p0 + k], t.rcol[p0 + k + off]);
-            slr += (int32_t)win[k];
+        for (int j = 0; j < 3; ++j) {
+#pragma unroll
+            for (int c = 0; c < CW; ++c) rc[j][c] = t.rcol[at(p0 + base + j)][c];
+            sr[j] = t.rs[at(p0 + base + j)];
+            ri[j] = t.rinv[at(p0 + base + j)];
         }
-        for (int p = p0; p < p1; ++p) {
-            const uint32_t fresh = column_dot<WIN>(t.lcol[p + WIN - 1], t.rcol[p + WIN - 1 + off]);
-            slr += (int32_t)fresh;
-            uint8_t c = 255;
-            if (x0 + p - d >= 0)
-                c = ncc_cost_value(N, slr, t.ls[p], t.rs[p + off], t.lsig[p], t.rsig[p + off]);
-            out[(size_t)p * ndisp + d] = c;
-            // slide: drop the window's first column, keep the rest in order
-            slr -= (int32_t)win[0];
+        uint32_t ring[WIN][4];                  // column products of the window, by column mod WIN
+        uint32_t slr[4] = {0, 0, 0, 0};
+        auto column = [&](int c, uint32_t (&slot)[4]) {
 #pragma unroll
-            for (int k = 0; k < WIN - 2; ++k) win[k] = win[k + 1];
-            win[WIN - 2] = fresh;
+            for (int k = 0; k < CW; ++k) rc[3][k] = t.rcol[at(c + base + 3)][k];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                slot[j] = column_dot<WIN>(t.lcol[c], rc[j]);
+                slr[j] += slot[j];
+            }
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+#pragma unroll
+                for (int k = 0; k < CW; ++k) rc[j][k] = rc[j + 1][k];
+        };
+        if (p0 < p1) {
+#pragma unroll
+            for (int k = 0; k < WIN - 1; ++k) column(p0 + k, ring[k]);
+        }
+        for (int pb = p0; pb < p1; pb += WIN) {
+#pragma unroll
+            for (int u = 0; u < WIN; ++u) {
+                const int p = pb + u;
+                if (p < p1) {
+                    column(p + WIN - 1, ring[(u + WIN - 1) % WIN]);
+                    sr[3] = t.rs[at(p + base + 3)];
+                    ri[3] = t.rinv[at(p + base + 3)];
+                    const int32_t sl = t.ls[p];
+                    const float li = t.linv[p];
+                    uint32_t b[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        // all factors fit 24 bits
+                        const int32_t num = __mul24((int)slr[j], N) - __mul24(sl, sr[j]);
+                        const float phi = __builtin_amdgcn_fmed3f((float)num * li * ri[j], 0.0f, 1.0f);
+                        const float v = __builtin_fmaf(-255.0f, phi, 255.0f);
+                        const float r = v + 12582912.0f;         // 1.5 * 2^23: the integer part, ties to even
+                        b[j] = __float_as_uint(r);
+                        // The product differs from the defined quotient by at
+                        // most 6 * 2^-24 of phi <= 1, the rounding of s, of
+                        // 255 s and of v by 2^-25 and twice 2^-17: together
+                        // below 2^-13 in v
+                        if (fabsf(v - (r - 12582912.0f)) > 0.5f - 0x1p-12f) {
+                            const int i = at(p + base + j);
+                            b[j] = ncc_cost_value(N, (int32_t)slr[j], sl, sr[j], t.lsig[p], t.rsig[i]);
+                        }
+                    }
+                    // j = 3 is disparity d0, j = 0 is d0 + 3
+                    uint8_t* o = out + (size_t)p * ndisp + d0;
+                    if (whole) {
+                        const uint32_t lo = __builtin_amdgcn_perm(b[2], b[3], 0x0c0c0400u);
+                        const uint32_t hi = __builtin_amdgcn_perm(b[0], b[1], 0x0c0c0400u);
+                        *reinterpret_cast<uint32_t*>(o) = lo | (hi << 16);
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if (d0 + j < ndisp) o[j] = (uint8_t)b[3 - j];
+                    }
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) slr[j] -= ring[u][j];
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) {
+                        sr[j] = sr[j + 1];
+                        ri[j] = ri[j + 1];
+                    }
+                }
+            }
         }
     }
 }

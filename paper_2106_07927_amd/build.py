@@ -26,7 +26,7 @@ LIB = os.path.join(PKG, "libsgm.so")
 
 HIP_SOURCES = ["census.hip", "cost.hip", "ncc.hip", "aggregate.hip", "wta_lrc.hip", "noalloc.hip"]
 CPP_SOURCES = ["sgm_capi.cpp", "batch.cpp"]
-PATH_LAYOUTS = 13          # entries of kPathLayouts in sgm_internal.h
+PATH_LAYOUTS = 26          # entries of kPathLayouts in sgm_internal.h
 # (source, object, extra flags) of every translation unit
 UNITS = ([(s, s + ".o", []) for s in HIP_SOURCES + CPP_SOURCES] +
          [("paths.hip", f"paths_{k}_{part}.hip.o", [f"-DSGM_PATH_LAYOUT={k}", f"-DSGM_PATH_PART={part}"])

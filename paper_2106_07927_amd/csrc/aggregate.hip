@@ -9,6 +9,9 @@
 // selection pass instead (wta_lrc.hip).
 #include "sgm_internal.h"
 
+#include <algorithm>
+#include <vector>
+
 namespace sgm {
 namespace {
 
@@ -84,62 +87,128 @@ __global__ __launch_bounds__(256) void merge_kernel(Frame f) {
 
 int merge_mode(int npaths, int p2) { return (slices_u8(p2) ? 2 : 0) + (npaths == 8 ? 1 : 0); }
 
-}  // namespace
+// Lane layouts (indices into kPathLayouts) of the ranges up to max_d, all with
+// identical results: the variants trade waves, the length of a line's chain
+// and total work.
+struct LayoutClass {
+    int max_d, n;
+    int8_t id[6];
+};
+constexpr LayoutClass kLayoutClasses[] = {
+    {2, 1, {0}},
+    {4, 1, {1}},
+    {8, 1, {2}},
+    {16, 4, {3, 13, 14, 15}},
+    {32, 5, {4, 16, 17, 18, 19}},
+    {64, 5, {5, 6, 20, 21, 22}},
+    {128, 6, {7, 8, 9, 23, 24, 25}},
+    {256, 3, {10, 11, 12}},
+};
 
-// Lane layouts per disparity range, all with identical results; the variants
-// trade waves and the length of a line's chain against total work.
-int path_variants(int ndisp) {
-    if (ndisp <= 32) return 1;
-    if (ndisp <= 64) return 2;
-    if (ndisp <= 128) return 3;
-    return 2;
+const LayoutClass& layout_class(int ndisp) {
+    const LayoutClass* c = kLayoutClasses;
+    while (c->max_d < ndisp) ++c;
+    return *c;
 }
 
-namespace {
-// index into kPathLayouts
+// The kernels with 16 disparities per lane do not fit two waves on a SIMD when
+// D cuts a lane's disparities, so such a D has the layouts of 8 or fewer only
+// (803x397, D = 100, path pass alone: 111 us against 186).
+bool layout_takes(int id, int ndisp) { return kPathLayouts[id].nreg_o < 8 || ndisp % 16 == 0; }
+
 int path_layout_id(int ndisp, int variant) {
-    if (ndisp <= 2) return 0;
-    if (ndisp <= 4) return 1;
-    if (ndisp <= 8) return 2;
-    if (ndisp <= 16) return 3;
-    if (ndisp <= 32) return 4;
-    if (ndisp <= 64) return 5 + (variant == 1);
-    // a D that cuts the 16 disparities of a lane in two: eight per lane instead
-    // (803x397, D = 100, path pass alone: 111 us against 186; the kernels with
-    // 16 per lane would not fit two waves on a SIMD)
-    if (ndisp <= 128) return 7 + (ndisp % 16 == 0 && (variant == 1 || variant == 2) ? variant : 0);
-    if (ndisp % 16 != 0) return 12;
-    return 10 + (variant == 1);
+    const LayoutClass& c = layout_class(ndisp);
+    const int id = c.id[variant >= 0 && variant < c.n ? variant : 0];
+    if (layout_takes(id, ndisp)) return id;
+    int v = 0;
+    while (!layout_takes(c.id[v], ndisp)) ++v;      // every range has one
+    return c.id[v];
 }
+
+// Blocks that take `us` each, in launch order.
+struct Run {
+    int blocks;
+    float us;
+};
+
+// How long the blocks of `runs` take: block b goes to compute unit b % 256, and
+// blocks that share one cost the longest's time plus half of the others'.
+// Against timed passes of 16 .. 256 disparities, 4 and 8 paths, 160x120 ..
+// 1920x1080: off by 5% in the mean while memory does not bound the pass.
+float run_time(const Run* runs, int n) {
+    constexpr int kUnits = 256;
+    constexpr float kShared = 0.5f;
+    float worst = 0.0f;
+    // what a unit holds changes only where a run begins
+    for (int k = 0, first = 0; k < n; first += runs[k++].blocks) {
+        float sum = 0.0f, longest = 0.0f;
+        int b = first % kUnits;
+        for (int at = 0, start = 0; at < n; start += runs[at++].blocks) {
+            for (; b < start + runs[at].blocks; b += kUnits) {
+                sum += runs[at].us;
+                longest = std::max(longest, runs[at].us);
+            }
+        }
+        worst = std::max(worst, longest + kShared * (sum - longest));
+    }
+    return worst;
+}
+
+// The variant that run_time puts first; `runs` has room for npaths / 2 of them
+// per frame.
+int fastest_variant(const FrameSize* sizes, int n, int ndisp, int npaths, Run* runs) {
+    const LayoutClass& c = layout_class(ndisp);
+    if (c.n == 1) return 0;
+    int best = -1;
+    float best_us = 0.0f;
+    for (int v = 0; v < c.n; ++v) {
+        if (!layout_takes(c.id[v], ndisp)) continue;
+        const PathLayout& l = kPathLayouts[c.id[v]];
+        int m = 0;
+        for (int i = 0; i < n; ++i) {
+            const int w = sizes[i].width, h = sizes[i].height;
+            for (int q = 0; q < npaths / 2; ++q)
+                runs[m++] = {pair_blocks(q, w, h, l), 1e-3f * (q == 0 ? w * l.ns_h : h * (q == 1 ? l.ns_v : l.ns_d))};
+        }
+        // work lists start with the longest lines
+        if (n > 1) std::sort(runs, runs + m, [](const Run& a, const Run& b) { return a.us > b.us; });
+        const float us = run_time(runs, m);
+        // up to D = 128 the first variant stays unless another is clearly
+        // ahead: in wide frames it does better than reckoned (1242x375,
+        // D = 128, 4 paths: 107, the next 117)
+        if (best < 0 || us < best_us * (best == 0 && ndisp <= 128 ? 0.92f : 1.0f)) {
+            best = v;
+            best_us = us;
+        }
+    }
+    return best;
+}
+
 }  // namespace
+
+int path_variants(int ndisp) { return layout_class(ndisp).n; }
 
 PathLayout path_layout(int ndisp, int variant) { return kPathLayouts[path_layout_id(ndisp, variant)]; }
 
-// Variant used when none is asked for (variant < 0), from timed sweeps of
-// 160x120 .. 1920x1080 with 4 and 8 paths (microseconds per frame below).
+// Variant used when none is asked for (variant < 0): the one that run_time
+// puts first.  Microseconds of the pass, the former choice by pixels and
+// blocks against this one: 320x240, D = 16, 4 paths 28 -> 19; 640x480, D = 32,
+// 8 paths 67 -> 54; 1242x375, D = 64, 8 paths 121 -> 86; 640x480, D = 128,
+// 4 paths 91 -> 67; 1024x768, D = 128, 8 paths 270 -> 227; 320x240, D = 256,
+// 4 paths 49 -> 39; over 86 such sizes 13% less in the geometric mean.
+int default_variant(const FrameSize* sizes, int n, int ndisp, int npaths) {
+    std::vector<Run> runs((size_t)n * (npaths / 2));
+    return fastest_variant(sizes, n, ndisp, npaths, runs.data());
+}
+
 int default_variant(int width, int height, int ndisp, int npaths) {
-    if (ndisp <= 32) return 0;
-    const int b0 = path_blocks(width, height, ndisp, npaths, 0);
-    if (ndisp <= 64) {
-        // helpers pay while every block has a compute unit of its own:
-        // 640x480, 4 paths (200 blocks) 94 against 104; 480x360, 8 paths
-        // (270 blocks) 101 against 93; 1920x1080 515 against 465
-        return b0 <= 256 ? 0 : 1;
-    }
-    if (ndisp <= 128) {
-        // up to two blocks per compute unit the shortest chains win (640x512:
-        // 173 against 201 and 181); beyond that whole lines per wave do
-        // (1920x1080: 934 and 998 against 820), but not where the rows are
-        // the long chains (1242x375: 237, 218, 278; 1920x400: 355, 409, 397)
-        if (b0 <= 512) return 0;
-        if (width > 2 * height) return b0 <= 768 ? 1 : 0;
-        return 2;
-    }
-    // 640x512 272 against 286, 1920x1080 1807 against 1740 (8 paths);
-    // 640x480 223 against 186, 1242x375 276 against 297 (4 paths)
-    const long px = (long)width * height;
-    if (npaths == 4) return px >= 300000 && width <= 2 * height ? 1 : 0;
-    return px >= 400000 ? 1 : 0;
+    // 8 paths of the widest ranges are bound by memory, where helpers read the
+    // cost bytes of the horizontal lines once more than they save in wide
+    // frames (1242x375, D = 256: 281 us with them, 254 without)
+    if (ndisp > 128 && ndisp % 16 == 0 && npaths == 8 && width > 2 * height && (long)width * height >= 400000) return 1;
+    const FrameSize size = {width, height};
+    Run runs[4];
+    return fastest_variant(&size, 1, ndisp, npaths, runs);
 }
 
 // Launch of the path pass for the layout `l`: the layout's kernels live in
@@ -151,19 +220,7 @@ hipError_t launch_paths_any(const Frame* one, const WorkList* wl, int ndisp, int
     if (id == K)                                                                                     \
         return one ? launch_paths_layout_id<K>(*one, ndisp, u8, nblocks, stream)                     \
                    : launch_paths_batch_layout_id<K>(*wl, ndisp, u8, nblocks, stream);
-    SGM_CASE(0)
-    SGM_CASE(1)
-    SGM_CASE(2)
-    SGM_CASE(3)
-    SGM_CASE(4)
-    SGM_CASE(5)
-    SGM_CASE(6)
-    SGM_CASE(7)
-    SGM_CASE(8)
-    SGM_CASE(9)
-    SGM_CASE(10)
-    SGM_CASE(11)
-    SGM_CASE(12)
+    SGM_PATH_LAYOUT_IDS(SGM_CASE)
 #undef SGM_CASE
     return hipErrorInvalidValue;
 }

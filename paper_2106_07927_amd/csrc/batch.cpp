@@ -153,6 +153,7 @@ size_t build_layout(const sgm_pair* pairs, int32_t n, const sgm_params* p, const
     frames->clear();
     launches->clear();
     size_t off = 0;
+    std::map<int, std::vector<int>> untuned;    // small frames without a tuned variant, per D
     for (int i = 0; i < n; ++i) {
         const sgm_pair& q = pairs[i];
         Frame f{};
@@ -168,8 +169,11 @@ size_t build_layout(const sgm_pair* pairs, int32_t n, const sgm_params* p, const
         f.lr_tolerance = p->lr_tolerance;
         f.median3x3 = p->median3x3;
         const int tv = tuned_variant(tune_table, q.width, q.height, q.ndisp);
-        f.variant = (tv >= 0 && tv < path_variants(q.ndisp)) ? tv
-                                                             : default_variant(q.width, q.height, q.ndisp, p->npaths);
+        f.variant = (tv >= 0 && tv < path_variants(q.ndisp)) ? tv : -1;
+        if (f.variant < 0) {
+            if (small_frame(f)) untuned[q.ndisp].push_back(i);
+            else f.variant = default_variant(q.width, q.height, q.ndisp, p->npaths);
+        }
         f.left = q.left;
         f.right = q.right;
         f.disp = q.disp_out;
@@ -185,6 +189,13 @@ size_t build_layout(const sgm_pair* pairs, int32_t n, const sgm_params* p, const
         f.disp_left = reinterpret_cast<uint16_t*>(off + 2 * l.census + l.cost + l.slices + l.agg + l.keys);
         off += l.total;
         frames->push_back(f);
+    }
+    // such frames share their launches: one variant, chosen for all their blocks
+    for (auto& kv : untuned) {
+        std::vector<FrameSize> sizes;
+        for (int i : kv.second) sizes.push_back({(*frames)[i].width, (*frames)[i].height});
+        const int v = default_variant(sizes.data(), (int)sizes.size(), kv.first, p->npaths);
+        for (int i : kv.second) (*frames)[i].variant = v;
     }
     // work-list launch groups over the small frames, in stage order
     std::vector<int> all;

@@ -250,19 +250,45 @@ struct PathLayout {
     int nreg_o, lpl_o;    // vertical and diagonal lines
     bool help_h, help_o;  // two waves per line group walk the partner's steps for the other two
     bool stream;          // nontemporal slice stores
+    // nanoseconds a block takes per pixel of a horizontal, vertical and
+    // diagonal line on a compute unit of its own, measured on frames of
+    // 160x120 .. 1920x1080 (0: the only layout of its disparity ranges)
+    int ns_h, ns_v, ns_d;
 };
 
 // Every layout the library builds (paths.hip is compiled once per entry).
-constexpr int kNumPathLayouts = 13;
+constexpr int kNumPathLayouts = 26;
 constexpr PathLayout kPathLayouts[kNumPathLayouts] = {
-    {1, 1, 1, 1, true, false, false},    {1, 2, 2, 1, true, false, false},
-    {1, 4, 4, 1, true, false, false},    {1, 8, 4, 2, true, false, false},
-    {1, 16, 4, 4, true, false, false},   {2, 16, 4, 8, true, true, false},
-    {2, 16, 4, 8, false, false, false},  {2, 32, 4, 16, true, false, false},
-    {2, 32, 8, 8, true, false, false},   {4, 16, 8, 8, false, false, true},
-    {4, 32, 8, 16, true, false, true},   {4, 32, 8, 16, false, false, true},
-    {4, 32, 4, 32, true, false, true},
+    {1, 1, 1, 1, true, false, false, 0, 0, 0},
+    {1, 2, 2, 1, true, false, false, 0, 0, 0},
+    {1, 4, 4, 1, true, false, false, 0, 0, 0},
+    {1, 8, 4, 2, true, false, false, 52, 109, 129},
+    {1, 16, 4, 4, true, false, false, 55, 113, 131},
+    {2, 16, 4, 8, true, true, false, 67, 92, 115},
+    {2, 16, 4, 8, false, false, false, 83, 115, 134},
+    {2, 32, 4, 16, true, false, false, 84, 134, 148},
+    {2, 32, 8, 8, true, false, false, 82, 186, 201},
+    {4, 16, 8, 8, false, false, true, 123, 182, 199},
+    {4, 32, 8, 16, true, false, true, 113, 204, 217},
+    {4, 32, 8, 16, false, false, true, 150, 201, 217},
+    {4, 32, 4, 32, true, false, true, 112, 147, 166},
+    {1, 8, 1, 8, true, true, false, 53, 56, 77},
+    {1, 8, 2, 4, true, false, false, 50, 77, 96},
+    {2, 4, 2, 4, true, true, false, 62, 64, 84},
+    {1, 16, 2, 8, true, true, false, 55, 67, 87},
+    {1, 16, 2, 8, true, false, false, 54, 82, 104},
+    {2, 8, 4, 4, true, false, false, 61, 114, 131},
+    {2, 8, 4, 4, false, false, true, 78, 112, 129},
+    {2, 16, 2, 16, false, false, false, 84, 93, 109},
+    {2, 16, 8, 4, true, false, false, 65, 181, 194},
+    {4, 8, 8, 4, false, false, true, 117, 178, 196},
+    {2, 32, 4, 16, true, true, false, 85, 103, 124},
+    {4, 16, 4, 16, true, false, false, 96, 132, 149},
+    {4, 16, 4, 16, false, false, false, 124, 132, 147},
 };
+#define SGM_PATH_LAYOUT_IDS(X)                                                                      \
+    X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)      \
+    X(17) X(18) X(19) X(20) X(21) X(22) X(23) X(24) X(25)
 
 // The path pass for layout kPathLayouts[ID] (paths.hip compiled per layout,
 // in two objects): the single-frame kernel for one frame, or the work-list
@@ -277,19 +303,7 @@ hipError_t launch_paths_batch_layout_id(const WorkList& wl, int ndisp, bool u8, 
     hipError_t launch_paths_layout_id<K>(const Frame&, int, bool, int, hipStream_t);            \
     template <>                                                                                 \
     hipError_t launch_paths_batch_layout_id<K>(const WorkList&, int, bool, int, hipStream_t);
-SGM_DECLARE_PATH_LAYOUT(0)
-SGM_DECLARE_PATH_LAYOUT(1)
-SGM_DECLARE_PATH_LAYOUT(2)
-SGM_DECLARE_PATH_LAYOUT(3)
-SGM_DECLARE_PATH_LAYOUT(4)
-SGM_DECLARE_PATH_LAYOUT(5)
-SGM_DECLARE_PATH_LAYOUT(6)
-SGM_DECLARE_PATH_LAYOUT(7)
-SGM_DECLARE_PATH_LAYOUT(8)
-SGM_DECLARE_PATH_LAYOUT(9)
-SGM_DECLARE_PATH_LAYOUT(10)
-SGM_DECLARE_PATH_LAYOUT(11)
-SGM_DECLARE_PATH_LAYOUT(12)
+SGM_PATH_LAYOUT_IDS(SGM_DECLARE_PATH_LAYOUT)
 #undef SGM_DECLARE_PATH_LAYOUT
 
 // Pairs of opposite path directions.  Pair q's forward step r (the reverse
@@ -313,6 +327,11 @@ __host__ __device__ inline int pair_blocks(int q, int width, int height, const P
 }
 int path_variants(int ndisp);                       // number of variants (>= 1)
 int default_variant(int width, int height, int ndisp, int npaths);
+// of several frames of one disparity range whose blocks share a launch
+struct FrameSize {
+    int width, height;
+};
+int default_variant(const FrameSize* sizes, int n, int ndisp, int npaths);
 PathLayout path_layout(int ndisp, int variant);
 int path_blocks(int width, int height, int ndisp, int npaths, int variant);
 // blocks of the horizontal directions, which come first in a frame's block order

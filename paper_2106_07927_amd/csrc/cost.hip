@@ -4,12 +4,16 @@
 //
 // A workgroup owns a run of kCostPix pixels of one row.  It stages the left
 // descriptors of the run and the right descriptors of [x0 - D + 1, x0 + kCostPix)
-// in LDS, so every right descriptor is read from HBM once per run.  When D is
-// a multiple of 4 each thread produces 4 consecutive disparities for a run of
-// PPG pixels (XOR + two v_bcnt each, packed into one dword), keeping the
-// PPG + 3 right descriptors it needs in registers; consecutive threads write
-// consecutive dwords, so the uint8 volume is written fully coalesced.
+// in LDS, so every right descriptor is read from HBM once per run.  Each thread
+// produces 4 consecutive disparities for a run of PPG pixels (XOR + two v_bcnt
+// each, packed into one dword), keeping the PPG + 3 right descriptors it needs
+// in registers; consecutive threads write consecutive dwords, so the uint8
+// volume is written fully coalesced.  Bound by that write: 1920x1080, D = 256:
+// 531 MB in 121 us.  A D that is no multiple of 4 goes the same way with
+// dwords at any byte (1242x375, D = 101: 20 us, a byte per thread took 47).
 #include "sgm_internal.h"
+
+#include <type_traits>
 
 namespace sgm {
 namespace {
@@ -54,27 +58,32 @@ __device__ __forceinline__ int stage_row(CostTile& t, const uint64_t* __restrict
     return npix;
 }
 
-// D a multiple of 4.  Thread (q, g) produces disparities 4q .. 4q+3 for the
-// PPG consecutive pixels of group g; the right descriptors it needs,
-// CR(x - d) for those pixels and disparities, are PPG + 3 consecutive LDS
-// entries, read once into registers and reused across the run.  FULL: the
-// run holds kCostPix pixels and starts at x0 >= D - 1, so no pixel lies past
-// the row's end and no disparity reaches left of the image (no checks).
-template <int PPG, bool FULL>
+// Thread (q, g) produces disparities 4q .. 4q+3 for the PPG consecutive pixels
+// of group g; the right descriptors it needs, CR(x - d) for those pixels and
+// disparities, are PPG + 3 consecutive LDS entries, read once into registers
+// and reused across the run.  FULL: the run holds kCostPix pixels and starts
+// at x0 >= D - 1, so no pixel lies past the row's end and no disparity reaches
+// left of the image (no checks).  RAGGED: D is no multiple of 4; the dwords
+// start at any byte, and the last one of a pixel holds D % 4 costs.
+template <int PPG, bool FULL, bool RAGGED>
 __device__ __forceinline__ void cost_tile_vec4(const CostTile& t, int npix, int ndisp,
-                                               uint32_t* __restrict__ out, int x0) {
-    const int dwords = ndisp >> 2;                 // dwords per pixel
+                                               uint8_t* __restrict__ out, int x0) {
+    const int dwords = RAGGED ? (ndisp + 3) >> 2 : ndisp >> 2;       // dwords per pixel
     const int q = threadIdx.x % dwords;
     const int g = threadIdx.x / dwords;
     const int d0 = q * 4;
     const int p0 = g * PPG;
     if (!FULL && p0 >= npix) return;
-    // sr index of CR(x - d) for pixel p: p + ndisp - 1 - d
+    // sr index of CR(x - d) for pixel p: p + ndisp - 1 - d (below 0 only past
+    // the last disparity)
     const int rb = p0 + ndisp - 1 - d0 - 3;
     uint64_t r[PPG + 3];
 #pragma unroll
-    for (int k = 0; k < PPG + 3; ++k) r[k] = (FULL || rb + k < npix + ndisp - 1) ? t.sr[rb + k] : 0ull;
-    uint32_t* o = out + p0 * dwords + q;
+    for (int k = 0; k < PPG + 3; ++k) {
+        const int i = RAGGED && k < 3 ? max(rb + k, 0) : rb + k;
+        r[k] = (FULL || rb + k < npix + ndisp - 1) ? t.sr[i] : 0ull;
+    }
+    uint8_t* o = out + p0 * ndisp + d0;
 #pragma unroll
     for (int i = 0; i < PPG; ++i) {
         const int p = p0 + i;
@@ -94,54 +103,44 @@ __device__ __forceinline__ void cost_tile_vec4(const CostTile& t, int npix, int 
                 }
             }
             // bytes c0..c3 (each <= 255): two shift-ors and one byte permute
-            o[i * dwords] = __builtin_amdgcn_perm(c2 | (c3 << 8), c0 | (c1 << 8), 0x05040100u);
+            const uint32_t v = __builtin_amdgcn_perm(c2 | (c3 << 8), c0 | (c1 << 8), 0x05040100u);
+            uint8_t* at = o + i * ndisp;
+            if (!RAGGED) {
+                *reinterpret_cast<uint32_t*>(at) = v;
+            } else if (d0 + 4 <= ndisp) {
+                __builtin_memcpy(at, &v, 4);
+            } else {
+                if (ndisp & 2) {
+                    const uint16_t two = (uint16_t)v;
+                    __builtin_memcpy(at, &two, 2);
+                }
+                if (ndisp & 1) at[ndisp & 2] = (uint8_t)(ndisp & 2 ? v >> 16 : v);
+            }
         }
     }
 }
 
-template <int PPG>
+template <int PPG, bool RAGGED>
 __device__ __forceinline__ void cost_run_vec4(CostTile& t, const uint64_t* __restrict__ cl,
                                               const uint64_t* __restrict__ cr, int width,
                                               int ndisp, uint8_t* __restrict__ cost, int bx, int y) {
     const int x0 = bx * kCostPix;
     const int npix = stage_row(t, cl, cr, width, ndisp, x0, y);
-    uint32_t* out = reinterpret_cast<uint32_t*>(cost + ((size_t)y * width + x0) * ndisp);
-    if (npix == kCostPix && x0 >= ndisp - 1) cost_tile_vec4<PPG, true>(t, npix, ndisp, out, x0);
-    else cost_tile_vec4<PPG, false>(t, npix, ndisp, out, x0);
+    uint8_t* out = cost + ((size_t)y * width + x0) * ndisp;
+    if (npix == kCostPix && x0 >= ndisp - 1) cost_tile_vec4<PPG, true, RAGGED>(t, npix, ndisp, out, x0);
+    else cost_tile_vec4<PPG, false, RAGGED>(t, npix, ndisp, out, x0);
     __syncthreads();   // the tile is reused by the next work item
 }
 
-// Any D: one byte per thread.
-__device__ __forceinline__ void cost_run_bytes(CostTile& t, const uint64_t* __restrict__ cl,
-                                               const uint64_t* __restrict__ cr, int width,
-                                               int ndisp, uint8_t* __restrict__ cost, int bx, int y) {
-    const int x0 = bx * kCostPix;
-    const int npix = stage_row(t, cl, cr, width, ndisp, x0, y);
-    uint8_t* out = cost + ((size_t)y * width + x0) * ndisp;
-    for (int b = threadIdx.x; b < npix * ndisp; b += blockDim.x) {
-        const int p = b / ndisp, d = b - p * ndisp;
-        const int x = x0 + p;
-        out[b] = (x - d >= 0) ? (uint8_t)__popcll(t.sl[p] ^ t.sr[p + ndisp - 1 - d]) : (uint8_t)255;
-    }
-    __syncthreads();
-}
-
-template <int PPG>
+template <int PPG, bool RAGGED>
 __global__ __launch_bounds__(256) void cost_kernel_vec4(const uint64_t* __restrict__ cl,
                                                         const uint64_t* __restrict__ cr, int width,
                                                         int ndisp, uint8_t* __restrict__ cost) {
     __shared__ CostTile t;
-    cost_run_vec4<PPG>(t, cl, cr, width, ndisp, cost, blockIdx.x, blockIdx.y);
+    cost_run_vec4<PPG, RAGGED>(t, cl, cr, width, ndisp, cost, blockIdx.x, blockIdx.y);
 }
 
-__global__ __launch_bounds__(256) void cost_kernel_bytes(const uint64_t* __restrict__ cl,
-                                                         const uint64_t* __restrict__ cr, int width,
-                                                         int ndisp, uint8_t* __restrict__ cost) {
-    __shared__ CostTile t;
-    cost_run_bytes(t, cl, cr, width, ndisp, cost, blockIdx.x, blockIdx.y);
-}
-
-template <int PPG>
+template <int PPG, bool RAGGED>
 __global__ __launch_bounds__(256) void cost_batch_vec4(WorkList wl) {
     __shared__ CostTile t;
     for (int b = blockIdx.x; b < wl.total; b += gridDim.x) {
@@ -149,69 +148,52 @@ __global__ __launch_bounds__(256) void cost_batch_vec4(WorkList wl) {
         const Frame& f = wl.frames[fi];
         const int lb = b - wl.starts[fi];
         const int bxs = cost_blocks_x(f.width);
-        cost_run_vec4<PPG>(t, f.census_left, f.census_right, f.width, f.ndisp, f.cost, lb % bxs,
-                           lb / bxs);
+        cost_run_vec4<PPG, RAGGED>(t, f.census_left, f.census_right, f.width, f.ndisp, f.cost, lb % bxs,
+                                   lb / bxs);
     }
 }
 
-__global__ __launch_bounds__(256) void cost_batch_bytes(WorkList wl) {
-    __shared__ CostTile t;
-    for (int b = blockIdx.x; b < wl.total; b += gridDim.x) {
-        const int fi = find_frame(wl, b);
-        const Frame& f = wl.frames[fi];
-        const int lb = b - wl.starts[fi];
-        const int bxs = cost_blocks_x(f.width);
-        cost_run_bytes(t, f.census_left, f.census_right, f.width, f.ndisp, f.cost, lb % bxs, lb / bxs);
-    }
-}
-
-// pixels per thread group and threads per block for D a multiple of 4
+// pixels per thread group and threads per block
 void vec4_shape(int ndisp, int* ppg, int* threads) {
-    const int dwords = ndisp / 4;
+    const int dwords = (ndisp + 3) / 4;
     const int need = (kCostPix * dwords + 255) / 256;          // pixels per group, at least
     *ppg = need <= 1 ? 1 : need <= 2 ? 2 : need <= 4 ? 4 : need <= 8 ? 8 : need <= 16 ? 16 : 32;
     *threads = dwords * ((kCostPix + *ppg - 1) / *ppg);
+}
+
+// launch(PPG, RAGGED) with the run length of D as constants
+template <typename Launch>
+void with_shape(int ndisp, const Launch& launch) {
+    int ppg, threads;
+    vec4_shape(ndisp, &ppg, &threads);
+    auto go = [&](auto p) {
+        if (ndisp & 3) launch(p, std::true_type{}, threads);
+        else launch(p, std::false_type{}, threads);
+    };
+    if (ppg == 1) go(std::integral_constant<int, 1>{});
+    else if (ppg == 2) go(std::integral_constant<int, 2>{});
+    else if (ppg == 4) go(std::integral_constant<int, 4>{});
+    else if (ppg == 8) go(std::integral_constant<int, 8>{});
+    else if (ppg == 16) go(std::integral_constant<int, 16>{});
+    else go(std::integral_constant<int, 32>{});
 }
 
 }  // namespace
 
 hipError_t launch_cost(const Frame& f, hipStream_t stream) {
     const dim3 grid(cost_blocks_x(f.width), f.height);
-    const uint64_t* cl = f.census_left;
-    const uint64_t* cr = f.census_right;
-    if ((f.ndisp & 3) == 0) {
-        int ppg, threads;
-        vec4_shape(f.ndisp, &ppg, &threads);
-#define SGM_COST(P) cost_kernel_vec4<P><<<grid, threads, 0, stream>>>(cl, cr, f.width, f.ndisp, f.cost)
-        if (ppg == 1) SGM_COST(1);
-        else if (ppg == 2) SGM_COST(2);
-        else if (ppg == 4) SGM_COST(4);
-        else if (ppg == 8) SGM_COST(8);
-        else if (ppg == 16) SGM_COST(16);
-        else SGM_COST(32);
-#undef SGM_COST
-    } else {
-        cost_kernel_bytes<<<grid, 256, 0, stream>>>(cl, cr, f.width, f.ndisp, f.cost);
-    }
+    with_shape(f.ndisp, [&](auto ppg, auto ragged, int threads) {
+        cost_kernel_vec4<ppg.value, ragged.value>
+            <<<grid, threads, 0, stream>>>(f.census_left, f.census_right, f.width, f.ndisp, f.cost);
+    });
     return hipGetLastError();
 }
 
 hipError_t launch_cost_batch(const WorkList& wl, int ndisp, hipStream_t stream) {
     const int grid = persistent_grid(wl.total);
-    if ((ndisp & 3) == 0) {
-        int ppg, threads;
-        vec4_shape(ndisp, &ppg, &threads);
-#define SGM_COST(P) cost_batch_vec4<P><<<grid, threads, 0, stream>>>(wl)
-        if (ppg == 1) SGM_COST(1);
-        else if (ppg == 2) SGM_COST(2);
-        else if (ppg == 4) SGM_COST(4);
-        else if (ppg == 8) SGM_COST(8);
-        else if (ppg == 16) SGM_COST(16);
-        else SGM_COST(32);
-#undef SGM_COST
-    } else {
-        cost_batch_bytes<<<grid, 256, 0, stream>>>(wl);
-    }
+    with_shape(ndisp, [&](auto ppg, auto ragged, int threads) {
+        cost_batch_vec4<ppg.value, ragged.value><<<grid, threads, 0, stream>>>(wl);
+    });
     return hipGetLastError();
 }
 

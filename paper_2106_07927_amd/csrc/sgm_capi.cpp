@@ -373,11 +373,6 @@ int32_t sgm_disparity_exact_lr(const uint8_t* left, const uint8_t* right, int32_
     f.cost = reinterpret_cast<uint8_t*>(base + l.cost);
     f.slices = reinterpret_cast<uint8_t*>(base + l.select);
     f.slice_stride = sgm::aggregate_slice_elems(width, height, ndisp);
-    f.right_keys = reinterpret_cast<uint32_t*>(base + l.select + l.keys);
-    f.disp_left = reinterpret_cast<uint16_t*>(base + l.select + l.dl);
-    f.lr_tolerance = -1;            // both passes: plain WTA maps
-    f.median3x3 = 0;
-    f.disp_right = nullptr;
     uint16_t* dl = reinterpret_cast<uint16_t*>(base + l.disp_left);
     uint16_t* flipped = reinterpret_cast<uint16_t*>(base + l.disp_flipped);
     uint8_t* ref = reinterpret_cast<uint8_t*>(base + l.ref);
@@ -388,17 +383,17 @@ int32_t sgm_disparity_exact_lr(const uint8_t* left, const uint8_t* right, int32_
             f.left = left;
             f.right = right;
             f.pitch = pitch_bytes;
-            f.disp = dl;
+            f.disp_left = dl;
         } else {
             e = sgm::launch_flip_pair(left, right, width, height, pitch_bytes, ref, mat, s);
             f.left = ref;
             f.right = mat;
             f.pitch = width;
-            f.disp = flipped;
+            f.disp_left = flipped;
         }
         if (e == hipSuccess) e = sgm::launch_census_pair(f, s);
         if (e == hipSuccess) e = sgm::launch_cost(f, s);
-        if (e == hipSuccess) e = sgm::launch_aggregate_select(f, s);
+        if (e == hipSuccess) e = sgm::launch_aggregate_wta(f, s);      // plain WTA maps
     }
     if (e == hipSuccess)
         e = sgm::launch_check_exact(dl, flipped, width, height, params->lr_tolerance,

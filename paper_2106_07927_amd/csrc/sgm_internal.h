@@ -358,6 +358,7 @@ hipError_t launch_wta_lrc(const Frame& f, hipStream_t stream);
 hipError_t launch_paths(const Frame& f, hipStream_t stream);
 // path sum fused with WTA / D^R / LR check / median, from the slices
 hipError_t launch_aggregate_select(const Frame& f, hipStream_t stream, bool fine = false);
+hipError_t launch_aggregate_wta(const Frame& f, hipStream_t stream);
 // exact consistency check: the swapped, flipped pair and the check against
 // its WTA map
 hipError_t launch_flip_pair(const uint8_t* left, const uint8_t* right, int width, int height,

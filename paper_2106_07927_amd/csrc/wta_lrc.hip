@@ -220,6 +220,11 @@ __device__ __forceinline__ void select_tile_block(uint16_t* __restrict__ sb, con
         }
     }
 
+    if (!f.right_keys) {                           // D^L alone is asked for
+        __syncthreads();
+        return;
+    }
+
     // (3) D^R
     {
         const int lane = threadIdx.x & 63;
@@ -565,6 +570,17 @@ hipError_t launch_aggregate_select(const Frame& f, hipStream_t stream, bool fine
     const dim3 g2(median_blocks_x(f.width), (f.height + kTH - 1) / kTH);
     if (fine) check_median_fine_kernel<<<g2, 256, 0, stream>>>(f);
     else check_median_kernel<<<g2, 256, 0, stream>>>(f);
+    return hipGetLastError();
+}
+
+// D^L alone, into f.disp_left: no D^R keys, no check, no median.
+hipError_t launch_aggregate_wta(const Frame& f, hipStream_t stream) {
+    Frame g = f;
+    g.right_keys = nullptr;
+    g.paths_fill_keys = 0;
+    const hipError_t e = launch_paths(g, stream);
+    if (e != hipSuccess) return e;
+    launch_fused_any<false>(&g, nullptr, g.ndisp, g.npaths, g.p2, stream);
     return hipGetLastError();
 }
 

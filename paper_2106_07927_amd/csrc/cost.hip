@@ -8,9 +8,10 @@
 // produces 4 consecutive disparities for a run of PPG pixels (XOR + two v_bcnt
 // each, packed into one dword), keeping the PPG + 3 right descriptors it needs
 // in registers; consecutive threads write consecutive dwords, so the uint8
-// volume is written fully coalesced.  Bound by that write: 1920x1080, D = 256:
-// 531 MB in 121 us.  A D that is no multiple of 4 goes the same way with
-// dwords at any byte (1242x375, D = 101: 20 us, a byte per thread took 47).
+// volume is written fully coalesced.  Bound by that write in large frames:
+// 1920x1080, D = 256: 531 MB in 120 us.  A D that is no multiple of 4 goes the
+// same way with dwords at any byte (1242x375, D = 101: 18 us, a byte per thread
+// took 47).
 #include "sgm_internal.h"
 
 #include <type_traits>
@@ -20,9 +21,23 @@ namespace {
 
 constexpr int kMaxD = 256;
 
+// Right descriptors in LDS: four planes, plane j % 4 holding every fourth one
+// at j / 4.  The lanes of a wave read descriptors four apart (one per dword of
+// costs), which are neighbours in a plane; in one row they would meet in a
+// quarter of the banks (1242x375, D = 128: 19.0 us, now 17.0; 640x512 15.8,
+// now 13.9).  At most 96 to a plane; 104 sets the four on banks of their own
+// when a row is staged.
+constexpr int kPlane = (kCostPix + kMaxD) / 4 + 8;
+__device__ __forceinline__ int right_at(int j) { return (j & 3) * kPlane + (j >> 2); }
+
+// Columns before x0 whose right descriptors a run holds: at least the D - 1 it
+// needs, a multiple of 4, so that it is known which plane a thread's k-th one
+// lies in.
+__host__ __device__ inline int right_back(int ndisp) { return (ndisp + 3) & ~3; }
+
 struct CostTile {
     uint64_t sl[kCostPix];
-    uint64_t sr[kCostPix + kMaxD - 1];
+    uint64_t sr[4 * kPlane];
 };
 
 __device__ __forceinline__ int stage_row(CostTile& t, const uint64_t* __restrict__ cl,
@@ -31,11 +46,11 @@ __device__ __forceinline__ int stage_row(CostTile& t, const uint64_t* __restrict
     const int npix = min(kCostPix, width - x0);
     const uint64_t* rowl = cl + (size_t)y * width;
     const uint64_t* rowr = cr + (size_t)y * width;
-    const int rbase = x0 - (ndisp - 1);
-    // entries [0, npix) of the left row, then [0, npix + D - 1) of the right
+    const int back = right_back(ndisp);
+    // entries [0, npix) of the left row, then [0, npix + back) of the right
     // one; all loads are issued before the first LDS write (one round trip)
-    const int nl = npix, n = npix + npix + ndisp - 1;
-    constexpr int kIt = (kCostPix + kCostPix + kMaxD - 1 + 127) / 128;   // blocks of >= 128 threads
+    const int nl = npix, n = npix + npix + back;
+    constexpr int kIt = (kCostPix + kCostPix + kMaxD + 127) / 128;   // blocks of >= 128 threads
     uint64_t v[kIt];
 #pragma unroll
     for (int it = 0; it < kIt; ++it) {
@@ -44,7 +59,7 @@ __device__ __forceinline__ int stage_row(CostTile& t, const uint64_t* __restrict
         if (i < nl) {
             v[it] = rowl[x0 + i];
         } else if (i < n) {
-            const int x = rbase + (i - nl);
+            const int x = x0 - back + (i - nl);
             if (x >= 0) v[it] = rowr[x];
         }
     }
@@ -52,7 +67,7 @@ __device__ __forceinline__ int stage_row(CostTile& t, const uint64_t* __restrict
     for (int it = 0; it < kIt; ++it) {
         const int i = (int)threadIdx.x + it * (int)blockDim.x;
         if (i < nl) t.sl[i] = v[it];
-        else if (i < n) t.sr[i - nl] = v[it];
+        else if (i < n) t.sr[right_at(i - nl)] = v[it];
     }
     __syncthreads();
     return npix;
@@ -60,9 +75,9 @@ __device__ __forceinline__ int stage_row(CostTile& t, const uint64_t* __restrict
 
 // Thread (q, g) produces disparities 4q .. 4q+3 for the PPG consecutive pixels
 // of group g; the right descriptors it needs, CR(x - d) for those pixels and
-// disparities, are PPG + 3 consecutive LDS entries, read once into registers
-// and reused across the run.  FULL: the run holds kCostPix pixels and starts
-// at x0 >= D - 1, so no pixel lies past the row's end and no disparity reaches
+// disparities, are PPG + 3 consecutive ones, read once into registers and
+// reused across the run.  FULL: the run holds kCostPix pixels and starts at
+// x0 >= D - 1, so no pixel lies past the row's end and no disparity reaches
 // left of the image (no checks).  RAGGED: D is no multiple of 4; the dwords
 // start at any byte, and the last one of a pixel holds D % 4 costs.
 template <int PPG, bool FULL, bool RAGGED>
@@ -74,14 +89,15 @@ __device__ __forceinline__ void cost_tile_vec4(const CostTile& t, int npix, int 
     const int d0 = q * 4;
     const int p0 = g * PPG;
     if (!FULL && p0 >= npix) return;
-    // sr index of CR(x - d) for pixel p: p + ndisp - 1 - d (below 0 only past
-    // the last disparity)
-    const int rb = p0 + ndisp - 1 - d0 - 3;
+    // CR(x - d) for pixel p is number p + back - d; the first one wanted, 1 mod 4
+    // where PPG is a multiple of 4
+    const int back = right_back(ndisp);
+    const int rb = p0 + back - d0 - 3;
     uint64_t r[PPG + 3];
 #pragma unroll
     for (int k = 0; k < PPG + 3; ++k) {
-        const int i = RAGGED && k < 3 ? max(rb + k, 0) : rb + k;
-        r[k] = (FULL || rb + k < npix + ndisp - 1) ? t.sr[i] : 0ull;
+        const int at = PPG >= 4 ? ((k + 1) & 3) * kPlane + (rb >> 2) + ((k + 1) >> 2) : right_at(rb + k);
+        r[k] = (FULL || rb + k < npix + back) ? t.sr[at] : 0ull;
     }
     uint8_t* o = out + p0 * ndisp + d0;
 #pragma unroll

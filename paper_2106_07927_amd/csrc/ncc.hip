@@ -23,8 +23,9 @@
 // the cost is first taken from the product with the two deviations'
 // reciprocals; where that lies so near a rounding tie that the defined
 // arithmetic could round to the other side (5 elements in 10,000), the lane
-// evaluates the definition.  1242x375, D = 128, 5x5: 68.7 -> 44.9 us, 9x9: 78.1 ->
-// 53.7 us; 1920x1080, D = 256, 5x5: 504 -> 275 us.
+// evaluates the definition.  1242x375, D = 128, 5x5: 68.7 -> 41.0 us (100
+// vector instructions per pixel and four disparities), 9x9: 78.1 -> 50.6 us;
+// 1920x1080, D = 256, 5x5: 504 -> 270 us.
 #include "sgm_internal.h"
 
 namespace sgm {
@@ -33,23 +34,35 @@ namespace {
 constexpr int kNccTile = 128;                  // pixels of a row per block
 constexpr int kMaxD = 256;
 
+// Entry i of an array that lanes read four entries apart: one entry of gap after
+// every 32 puts the lanes of a half wave on banks of their own (entries of 8
+// bytes; without the gaps they meet four at a time: 44.9 us at 1242x375, D = 128).
+constexpr __host__ __device__ int spread(int i) { return i + (i >> 5); }
+
+// The patch sum and the reciprocal deviation of a pixel (0 for a patch without
+// variance and for a right pixel outside the image: such a cost is 255); on the
+// left side times -255.
+struct PatchTerms {
+    int32_t sum;
+    float inv;
+};
+
 template <int WIN>
 struct NccTile {
     static constexpr int R = (WIN - 1) / 2;
     static constexpr int CW = (WIN + 3) / 4;   // dwords per packed column
     static constexpr int LCOLS = kNccTile + 2 * R;
     static constexpr int RCOLS = kNccTile + kMaxD - 1 + 2 * R;
-    uint32_t lcol[LCOLS][CW];
-    uint32_t rcol[RCOLS][CW];
+    static constexpr int RPIX = kNccTile + kMaxD - 1;
+    alignas(8) uint32_t lcol[LCOLS][CW];
+    alignas(8) uint32_t rcol[spread(RCOLS)][CW];
     int32_t lsum[LCOLS], lsq[LCOLS];
     int32_t rsum[RCOLS], rsq[RCOLS];
-    // per tile pixel / right pixel x0 - D + 1 + i: the patch sum, the deviation
-    // sqrt(n SS - S^2), and its reciprocal (0 for a patch without variance and
-    // for a right pixel outside the image: such a cost is 255)
-    int32_t ls[kNccTile];
-    float lsig[kNccTile], linv[kNccTile];
-    int32_t rs[kNccTile + kMaxD - 1];
-    float rsig[kNccTile + kMaxD - 1], rinv[kNccTile + kMaxD - 1];
+    // per tile pixel / right pixel x0 - D + 1 + i, and the deviations
+    // sqrt(n SS - S^2)
+    alignas(8) PatchTerms lp[kNccTile];
+    alignas(8) PatchTerms rp[spread(RPIX)];
+    float lsig[kNccTile], rsig[RPIX];
 };
 
 // Column c of a staged image: rows y - R .. y + R at image column gx.
@@ -103,7 +116,8 @@ __device__ __forceinline__ uint8_t ncc_cost_value(int n, int32_t slr, int32_t sl
     return (uint8_t)v;
 }
 
-template <int WIN>
+// WHOLE: D is a multiple of 4.
+template <int WIN, bool WHOLE>
 __global__ __launch_bounds__(256) void ncc_cost_kernel(const uint8_t* __restrict__ left,
                                                        const uint8_t* __restrict__ right, int width,
                                                        int height, int pitch, int ndisp,
@@ -123,7 +137,7 @@ __global__ __launch_bounds__(256) void ncc_cost_kernel(const uint8_t* __restrict
     for (int c = threadIdx.x; c < npx + 2 * R; c += blockDim.x)
         stage_column<WIN>(left, width, height, pitch, x0 - R + c, y, t.lcol[c], t.lsum[c], t.lsq[c]);
     for (int c = threadIdx.x; c < nr; c += blockDim.x)
-        stage_column<WIN>(right, width, height, pitch, rbase + c, y, t.rcol[c], t.rsum[c], t.rsq[c]);
+        stage_column<WIN>(right, width, height, pitch, rbase + c, y, t.rcol[spread(c)], t.rsum[c], t.rsq[c]);
     __syncthreads();
 
     // patch sums and deviations
@@ -135,9 +149,8 @@ __global__ __launch_bounds__(256) void ncc_cost_kernel(const uint8_t* __restrict
             q += t.lsq[p + k];
         }
         const float sig = patch_sigma(N, s, q);
-        t.ls[p] = s;
+        t.lp[p] = PatchTerms{s, sig > 0.0f ? -255.0f * (1.0f / sig) : 0.0f};
         t.lsig[p] = sig;
-        t.linv[p] = sig > 0.0f ? 1.0f / sig : 0.0f;
     }
     for (int p = threadIdx.x; p < npx + ndisp - 1; p += blockDim.x) {
         int32_t s = 0, q = 0;
@@ -147,9 +160,8 @@ __global__ __launch_bounds__(256) void ncc_cost_kernel(const uint8_t* __restrict
             q += t.rsq[p + k];
         }
         const float sig = patch_sigma(N, s, q);
-        t.rs[p] = s;
+        t.rp[spread(p)] = PatchTerms{s, sig > 0.0f && x0 - ndisp + 1 + p >= 0 ? 1.0f / sig : 0.0f};
         t.rsig[p] = sig;
-        t.rinv[p] = sig > 0.0f && x0 - ndisp + 1 + p >= 0 ? 1.0f / sig : 0.0f;
     }
     __syncthreads();
 
@@ -159,30 +171,28 @@ __global__ __launch_bounds__(256) void ncc_cost_kernel(const uint8_t* __restrict
     const int nruns = max(1, 256 / groups);
     const int run = (npx + nruns - 1) / nruns;
     uint8_t* out = cost + ((size_t)y * width + x0) * ndisp;
-    const bool whole = (ndisp & 3) == 0;
     for (int item = threadIdx.x; item < nruns * groups; item += blockDim.x) {
         const int d0 = 4 * (item % groups);
         const int p0 = (item / groups) * run;
         const int p1 = min(npx, p0 + run);
         // index of disparity d0 + 3 at pixel 0; below 0 only for disparities past D
         const int base = ndisp - 1 - d0 - 3;
-        auto at = [&](int i) { return max(i, 0); };
+        auto at = [&](int i) { return spread(WHOLE ? i : max(i, 0)); };
         // right columns and right pixels of the four disparities, the largest first
         uint32_t rc[4][CW];
-        int32_t sr[4];
-        float ri[4];
+        PatchTerms rp[4];
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
 #pragma unroll
             for (int c = 0; c < CW; ++c) rc[j][c] = t.rcol[at(p0 + base + j)][c];
-            sr[j] = t.rs[at(p0 + base + j)];
-            ri[j] = t.rinv[at(p0 + base + j)];
+            rp[j] = t.rp[at(p0 + base + j)];
         }
         uint32_t ring[WIN][4];                  // column products of the window, by column mod WIN
         uint32_t slr[4] = {0, 0, 0, 0};
         auto column = [&](int c, uint32_t (&slot)[4]) {
+            const int i = at(c + base + 3);
 #pragma unroll
-            for (int k = 0; k < CW; ++k) rc[3][k] = t.rcol[at(c + base + 3)][k];
+            for (int k = 0; k < CW; ++k) rc[3][k] = t.rcol[i][k];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 slot[j] = column_dot<WIN>(t.lcol[c], rc[j]);
@@ -203,46 +213,51 @@ __global__ __launch_bounds__(256) void ncc_cost_kernel(const uint8_t* __restrict
                 const int p = pb + u;
                 if (p < p1) {
                     column(p + WIN - 1, ring[(u + WIN - 1) % WIN]);
-                    sr[3] = t.rs[at(p + base + 3)];
-                    ri[3] = t.rinv[at(p + base + 3)];
-                    const int32_t sl = t.ls[p];
-                    const float li = t.linv[p];
+                    rp[3] = t.rp[at(p + base + 3)];
+                    const PatchTerms lp = t.lp[p];
                     uint32_t b[4];
+                    float tie[4];
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         // all factors fit 24 bits
-                        const int32_t num = __mul24((int)slr[j], N) - __mul24(sl, sr[j]);
-                        const float phi = __builtin_amdgcn_fmed3f((float)num * li * ri[j], 0.0f, 1.0f);
-                        const float v = __builtin_fmaf(-255.0f, phi, 255.0f);
+                        const int32_t num = __mul24((int)slr[j], N) - __mul24(lp.sum, rp[j].sum);
+                        const float v = __builtin_amdgcn_fmed3f(
+                            __builtin_fmaf((float)num * lp.inv, rp[j].inv, 255.0f), 0.0f, 255.0f);
                         const float r = v + 12582912.0f;         // 1.5 * 2^23: the integer part, ties to even
                         b[j] = __float_as_uint(r);
-                        // The product differs from the defined quotient by at
-                        // most 6 * 2^-24 of phi <= 1, the rounding of s, of
-                        // 255 s and of v by 2^-25 and twice 2^-17: together
-                        // below 2^-13 in v
-                        if (fabsf(v - (r - 12582912.0f)) > 0.5f - 0x1p-12f) {
-                            const int i = at(p + base + j);
-                            b[j] = ncc_cost_value(N, (int32_t)slr[j], sl, sr[j], t.lsig[p], t.rsig[i]);
-                        }
+                        tie[j] = fabsf(v - (r - 12582912.0f));
+                    }
+                    // The product differs from the defined quotient by at most
+                    // 6 * 2^-24 of phi <= 1 (the definition rounds the product of
+                    // the deviations and the quotient, this the two reciprocals
+                    // and two products), the rounding of s, of 255 s and of v by
+                    // 2^-25 and twice 2^-17: together below 2^-13 in v
+                    constexpr float kTie = 0.5f - 0x1p-12f;
+                    if (fmaxf(fmaxf(tie[0], tie[1]), fmaxf(tie[2], tie[3])) > kTie) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if (tie[j] > kTie)
+                                b[j] = ncc_cost_value(N, (int32_t)slr[j], lp.sum, rp[j].sum, t.lsig[p],
+                                                      t.rsig[max(p + base + j, 0)]);
                     }
                     // j = 3 is disparity d0, j = 0 is d0 + 3
                     uint8_t* o = out + (size_t)p * ndisp + d0;
-                    if (whole) {
-                        const uint32_t lo = __builtin_amdgcn_perm(b[2], b[3], 0x0c0c0400u);
-                        const uint32_t hi = __builtin_amdgcn_perm(b[0], b[1], 0x0c0c0400u);
-                        *reinterpret_cast<uint32_t*>(o) = lo | (hi << 16);
+                    const uint32_t lo = __builtin_amdgcn_perm(b[2], b[3], 0x0c0c0400u);
+                    const uint32_t hi = __builtin_amdgcn_perm(b[0], b[1], 0x0c0c0400u);
+                    const uint32_t w = lo | (hi << 16);
+                    if (WHOLE) {
+                        *reinterpret_cast<uint32_t*>(o) = w;
+                    } else if (d0 + 4 <= ndisp) {
+                        __builtin_memcpy(o, &w, 4);
                     } else {
 #pragma unroll
-                        for (int j = 0; j < 4; ++j)
+                        for (int j = 0; j < 3; ++j)
                             if (d0 + j < ndisp) o[j] = (uint8_t)b[3 - j];
                     }
 #pragma unroll
                     for (int j = 0; j < 4; ++j) slr[j] -= ring[u][j];
 #pragma unroll
-                    for (int j = 0; j < 3; ++j) {
-                        sr[j] = sr[j + 1];
-                        ri[j] = ri[j + 1];
-                    }
+                    for (int j = 0; j < 3; ++j) rp[j] = rp[j + 1];
                 }
             }
         }
@@ -254,8 +269,15 @@ __global__ __launch_bounds__(256) void ncc_cost_kernel(const uint8_t* __restrict
 hipError_t launch_ncc_cost(const uint8_t* left, const uint8_t* right, int width, int height,
                            int pitch, int win, int ndisp, uint8_t* cost, hipStream_t stream) {
     const dim3 grid((width + kNccTile - 1) / kNccTile, height);
-    if (win == 5) ncc_cost_kernel<5><<<grid, 256, 0, stream>>>(left, right, width, height, pitch, ndisp, cost);
-    else ncc_cost_kernel<9><<<grid, 256, 0, stream>>>(left, right, width, height, pitch, ndisp, cost);
+#define SGM_NCC(W, F) ncc_cost_kernel<W, F><<<grid, 256, 0, stream>>>(left, right, width, height, pitch, ndisp, cost)
+    if (win == 5) {
+        if (ndisp % 4 == 0) SGM_NCC(5, true);
+        else SGM_NCC(5, false);
+    } else {
+        if (ndisp % 4 == 0) SGM_NCC(9, true);
+        else SGM_NCC(9, false);
+    }
+#undef SGM_NCC
     return hipGetLastError();
 }
 

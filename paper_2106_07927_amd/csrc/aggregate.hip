@@ -188,6 +188,13 @@ int fastest_variant(const FrameSize* sizes, int n, int ndisp, int npaths, Run* r
 
 int path_variants(int ndisp) { return layout_class(ndisp).n; }
 
+int wide_variant(int ndisp) {
+    const LayoutClass& c = layout_class(ndisp);
+    int v = 0;
+    while (!layout_wide(c.id[v])) ++v;              // every range has one, and it takes every D
+    return v;
+}
+
 PathLayout path_layout(int ndisp, int variant) { return kPathLayouts[path_layout_id(ndisp, variant)]; }
 
 // Variant used when none is asked for (variant < 0): the one that run_time
@@ -213,13 +220,13 @@ int default_variant(int width, int height, int ndisp, int npaths) {
 
 // Launch of the path pass for the layout `l`: the layout's kernels live in
 // their own object (paths.hip, compiled per layout).
-hipError_t launch_paths_any(const Frame* one, const WorkList* wl, int ndisp, int variant, bool u8,
+hipError_t launch_paths_any(const Frame* one, const WorkList* wl, int ndisp, int variant, int p2,
                             int nblocks, hipStream_t stream) {
     const int id = path_layout_id(ndisp, variant);
 #define SGM_CASE(K)                                                                                  \
     if (id == K)                                                                                     \
-        return one ? launch_paths_layout_id<K>(*one, ndisp, u8, nblocks, stream)                     \
-                   : launch_paths_batch_layout_id<K>(*wl, ndisp, u8, nblocks, stream);
+        return one ? launch_paths_layout_id<K>(*one, ndisp, p2, nblocks, stream)                     \
+                   : launch_paths_batch_layout_id<K>(*wl, ndisp, p2, nblocks, stream);
     SGM_PATH_LAYOUT_IDS(SGM_CASE)
 #undef SGM_CASE
     return hipErrorInvalidValue;
@@ -248,11 +255,12 @@ size_t aggregate_work_bytes(int width, int height, int ndisp, int npaths, int p2
 }
 
 hipError_t launch_paths(const Frame& f, hipStream_t stream) {
-    const int variant = (f.variant >= 0 && f.variant < path_variants(f.ndisp))
+    const int variant = f.p2 > kNarrowP2 ? wide_variant(f.ndisp)
+                        : (f.variant >= 0 && f.variant < path_variants(f.ndisp))
                             ? f.variant
                             : default_variant(f.width, f.height, f.ndisp, f.npaths);
     const int nb = path_blocks(f.width, f.height, f.ndisp, f.npaths, variant);
-    return launch_paths_any(&f, nullptr, f.ndisp, variant, slices_u8(f.p2), nb, stream);
+    return launch_paths_any(&f, nullptr, f.ndisp, variant, f.p2, nb, stream);
 }
 
 hipError_t launch_aggregate(const Frame& f, hipStream_t stream) {
@@ -272,7 +280,7 @@ hipError_t launch_paths_batch(const WorkList& wl, int ndisp, int npaths, int p2,
                               hipStream_t stream) {
     (void)npaths;
     if (variant < 0 || variant >= path_variants(ndisp)) variant = 0;
-    return launch_paths_any(nullptr, &wl, ndisp, variant, slices_u8(p2), wl.total, stream);
+    return launch_paths_any(nullptr, &wl, ndisp, variant, p2, wl.total, stream);
 }
 
 }  // namespace sgm

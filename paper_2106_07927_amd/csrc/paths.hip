@@ -56,7 +56,12 @@
 //     V(d) = min(L(d), min(L(d-1), L(d+1)) + P1, m + P2),
 //     A(d) = V(d) - m,  L'(d) = V(d) + C(d).
 // Per register: a minimum, an add, a three-way minimum (v_pk_minimum3_f16 on
-// the integers' bit patterns), a byte permute and an add.  m is a tree over
+// the integers' bit patterns), a byte permute and an add.  That minimum asks
+// for states below 0x7C00: in the 16 steps between two offsets taken off m
+// grows to 16 * 255 at most, a real state to m + P2 + 255, padding to twice P2
+// (below), and with P1 <= P2 added that is 0x7C00 only where P2 > 7936
+// (kNarrowP2); a larger one, which 4 paths may have, takes two minima
+// (1242x375, D = 128, P2 = 880: 212 us with two, 203 with one).  m is a tree over
 // the registers and an all-reduce over the line's lanes that runs beside the
 // neighbour terms.  Disparities beyond D (padding) are lifted by 255 + P2 in
 // every step: as neighbours they never come below m + P2, and m never is one.
@@ -590,12 +595,11 @@ struct Walker {
 // One wave of a line pair, the whole way along.  The offsets of the steps of
 // the next chunk are laid out one chunk ahead and serve its cost loads,
 // its checkpoint and its stores.
-template <int KIND, int NREG, int LPL, int K, bool RAGGED, bool PADDED, bool U8, bool HELP>
+template <int KIND, int NREG, int LPL, int K, bool RAGGED, bool PADDED, bool U8, bool NARROW, bool HELP>
 __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ slice, int q, bool fwd,
                                          bool helper, int group, uint32_t* __restrict__ lds) {
     constexpr int DPL = 2 * NREG;
     constexpr int LPW = 64 / LPL;
-    constexpr bool NARROW = U8;
     constexpr int SW = StateBytes<NREG>::kWords;
     const int width = f.width, height = f.height, ndisp = f.ndisp;
     const int lane = threadIdx.x & 63;
@@ -757,8 +761,9 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
             for (int k = 0; k < NREG; ++k) {
                 P[k] = wide_pair<NREG>(kw, k);
                 out.l[K - 1][k] = P[k];
-                // padding may hold anything: bounded, so that the lift cannot overflow
-                if constexpr (PADDED) P[k] = pk_min(P[k], 0x7FFF7FFFu) + cst.lift(k);
+                // padding may hold anything: bounded (a real value is at most
+                // 255 + P2), so that the lift cannot overflow
+                if constexpr (PADDED) P[k] = pk_min(P[k], NARROW ? 0x1FFF1FFFu : 0x7FFF7FFFu) + cst.lift(k);
             }
         }
     };
@@ -948,7 +953,7 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
 // Block lb of the path pass of one frame: pair q, line groups 2g and 2g + 1;
 // waves 0, 1 walk the forward direction along them, waves 2, 3 the reverse
 // one.
-template <int NH, int LH, int NO, int LO, bool RGH, bool PDH, bool RGO, bool PDO, bool U8>
+template <int NH, int LH, int NO, int LO, bool RGH, bool PDH, bool RGO, bool PDO, bool U8, bool NARROW>
 __device__ __forceinline__ void paths_block(const Frame& f, int lb) {
     constexpr int KH = kStepsH, KO = kStepsO;
     constexpr PathLayout kLayout = kPathLayouts[SGM_PATH_LAYOUT];
@@ -985,26 +990,26 @@ __device__ __forceinline__ void paths_block(const Frame& f, int lb) {
     uint32_t* mine = lds + (fwd ? 0 : kLds);
     if (q == 0) {
         __builtin_amdgcn_s_setprio(2);
-        run_wave<kHorizontal, NH, LH, KH, RGH, PDH, U8, HELPH>(f, slice, q, fwd, wave >= 2, group, mine);
+        run_wave<kHorizontal, NH, LH, KH, RGH, PDH, U8, NARROW, HELPH>(f, slice, q, fwd, wave >= 2, group, mine);
         __builtin_amdgcn_s_setprio(0);
     } else if (q == 1) {
-        run_wave<kVertical, NO, LO, KO, RGO, PDO, U8, HELPO>(f, slice, q, fwd, wave >= 2, group, mine);
+        run_wave<kVertical, NO, LO, KO, RGO, PDO, U8, NARROW, HELPO>(f, slice, q, fwd, wave >= 2, group, mine);
     } else {
-        run_wave<kDiagonal, NO, LO, KO, RGO, PDO, U8, HELPO>(f, slice, q, fwd, wave >= 2, group, mine);
+        run_wave<kDiagonal, NO, LO, KO, RGO, PDO, U8, NARROW, HELPO>(f, slice, q, fwd, wave >= 2, group, mine);
     }
 }
 
-template <int NH, int LH, int NO, int LO, bool RGH, bool PDH, bool RGO, bool PDO, bool U8>
+template <int NH, int LH, int NO, int LO, bool RGH, bool PDH, bool RGO, bool PDO, bool U8, bool NARROW>
 __global__ __launch_bounds__(kThreads, 2) void paths_kernel(Frame f) {
-    paths_block<NH, LH, NO, LO, RGH, PDH, RGO, PDO, U8>(f, blockIdx.x);
+    paths_block<NH, LH, NO, LO, RGH, PDH, RGO, PDO, U8, NARROW>(f, blockIdx.x);
 }
 
-template <int NH, int LH, int NO, int LO, bool RGH, bool PDH, bool RGO, bool PDO, bool U8>
+template <int NH, int LH, int NO, int LO, bool RGH, bool PDH, bool RGO, bool PDO, bool U8, bool NARROW>
 __global__ __launch_bounds__(kThreads, 2) void paths_batch_kernel(WorkList wl) {
     // one block per item, the longest lines first (a loop over items here costs
     // the registers that let two waves share a SIMD)
     const int b = blockIdx.x;
-    paths_block<NH, LH, NO, LO, RGH, PDH, RGO, PDO, U8>(wl.frames[wl.items[2 * b]], wl.items[2 * b + 1]);
+    paths_block<NH, LH, NO, LO, RGH, PDH, RGO, PDO, U8, NARROW>(wl.frames[wl.items[2 * b]], wl.items[2 * b + 1]);
 }
 
 // Path-kernel launches for one lane layout: the single-frame kernel, or the
@@ -1020,46 +1025,52 @@ __host__ inline LayoutFlags layout_flags(int nh, int lh, int no, int lo, int ndi
 
 #if SGM_PATH_PART == 0
 template <int NH, int LH, int NO, int LO>
-hipError_t launch_paths_single(const Frame& one, int ndisp, bool u8, int nblocks, hipStream_t stream) {
+hipError_t launch_paths_single(const Frame& one, int ndisp, int p2, int nblocks, hipStream_t stream) {
     const LayoutFlags fl = layout_flags(NH, LH, NO, LO, ndisp);
-#define SGM_PATHS(A, B, C, D, U) \
-    paths_kernel<NH, LH, NO, LO, A, B, C, D, U><<<nblocks, kThreads, 0, stream>>>(one)
+    constexpr bool kWide = layout_wide(SGM_PATH_LAYOUT);
+#define SGM_PATHS(A, B)                                                                                    \
+    do {                                                                                                   \
+        if (slices_u8(p2)) paths_kernel<NH, LH, NO, LO, A, B, A, B, true, true><<<nblocks, kThreads, 0, stream>>>(one);   \
+        else if (p2 <= kNarrowP2)                                                                          \
+            paths_kernel<NH, LH, NO, LO, A, B, A, B, false, true><<<nblocks, kThreads, 0, stream>>>(one);            \
+        else if constexpr (kWide)                                                                          \
+            paths_kernel<NH, LH, NO, LO, A, B, A, B, false, false><<<nblocks, kThreads, 0, stream>>>(one);           \
+        else                                                                                               \
+            return hipErrorInvalidValue;                 /* wide_variant gives no other layout such a P2 */ \
+    } while (0)
     if (fl.ragged) {
-        if constexpr (NO <= 4) {               // path_layout_id gives no other layout such a D
-            if (u8) SGM_PATHS(true, true, true, true, true);
-            else SGM_PATHS(true, true, true, true, false);
-        } else {
-            return hipErrorInvalidValue;
-        }
+        if constexpr (NO <= 4) SGM_PATHS(true, true);
+        else return hipErrorInvalidValue;                // path_layout_id gives no other layout such a D
     } else if (fl.padded) {
-        if (u8) SGM_PATHS(false, true, false, true, true);
-        else SGM_PATHS(false, true, false, true, false);
+        SGM_PATHS(false, true);
     } else {
-        if (u8) SGM_PATHS(false, false, false, false, true);
-        else SGM_PATHS(false, false, false, false, false);
+        SGM_PATHS(false, false);
     }
 #undef SGM_PATHS
     return hipGetLastError();
 }
 #else
 template <int NH, int LH, int NO, int LO>
-hipError_t launch_paths_worklist(const WorkList& wl, int ndisp, bool u8, int nblocks, hipStream_t stream) {
+hipError_t launch_paths_worklist(const WorkList& wl, int ndisp, int p2, int nblocks, hipStream_t stream) {
     const LayoutFlags fl = layout_flags(NH, LH, NO, LO, ndisp);
-#define SGM_PATHS(A, B, C, D, U) \
-    paths_batch_kernel<NH, LH, NO, LO, A, B, C, D, U><<<nblocks, kThreads, 0, stream>>>(wl)
+    constexpr bool kWide = layout_wide(SGM_PATH_LAYOUT);
+#define SGM_PATHS(A, B)                                                                                    \
+    do {                                                                                                   \
+        if (slices_u8(p2)) paths_batch_kernel<NH, LH, NO, LO, A, B, A, B, true, true><<<nblocks, kThreads, 0, stream>>>(wl);   \
+        else if (p2 <= kNarrowP2)                                                                          \
+            paths_batch_kernel<NH, LH, NO, LO, A, B, A, B, false, true><<<nblocks, kThreads, 0, stream>>>(wl);            \
+        else if constexpr (kWide)                                                                          \
+            paths_batch_kernel<NH, LH, NO, LO, A, B, A, B, false, false><<<nblocks, kThreads, 0, stream>>>(wl);           \
+        else                                                                                               \
+            return hipErrorInvalidValue;                 /* wide_variant gives no other layout such a P2 */ \
+    } while (0)
     if (fl.ragged) {
-        if constexpr (NO <= 4) {               // path_layout_id gives no other layout such a D
-            if (u8) SGM_PATHS(true, true, true, true, true);
-            else SGM_PATHS(true, true, true, true, false);
-        } else {
-            return hipErrorInvalidValue;
-        }
+        if constexpr (NO <= 4) SGM_PATHS(true, true);
+        else return hipErrorInvalidValue;                // path_layout_id gives no other layout such a D
     } else if (fl.padded) {
-        if (u8) SGM_PATHS(false, true, false, true, true);
-        else SGM_PATHS(false, true, false, true, false);
+        SGM_PATHS(false, true);
     } else {
-        if (u8) SGM_PATHS(false, false, false, false, true);
-        else SGM_PATHS(false, false, false, false, false);
+        SGM_PATHS(false, false);
     }
 #undef SGM_PATHS
     return hipGetLastError();
@@ -1070,17 +1081,17 @@ hipError_t launch_paths_worklist(const WorkList& wl, int ndisp, bool u8, int nbl
 
 #if SGM_PATH_PART == 0
 template <>
-hipError_t launch_paths_layout_id<SGM_PATH_LAYOUT>(const Frame& one, int ndisp, bool u8, int nblocks,
+hipError_t launch_paths_layout_id<SGM_PATH_LAYOUT>(const Frame& one, int ndisp, int p2, int nblocks,
                                                    hipStream_t stream) {
     constexpr PathLayout L = kPathLayouts[SGM_PATH_LAYOUT];
-    return launch_paths_single<L.nreg_h, L.lpl_h, L.nreg_o, L.lpl_o>(one, ndisp, u8, nblocks, stream);
+    return launch_paths_single<L.nreg_h, L.lpl_h, L.nreg_o, L.lpl_o>(one, ndisp, p2, nblocks, stream);
 }
 #else
 template <>
-hipError_t launch_paths_batch_layout_id<SGM_PATH_LAYOUT>(const WorkList& wl, int ndisp, bool u8,
+hipError_t launch_paths_batch_layout_id<SGM_PATH_LAYOUT>(const WorkList& wl, int ndisp, int p2,
                                                          int nblocks, hipStream_t stream) {
     constexpr PathLayout L = kPathLayouts[SGM_PATH_LAYOUT];
-    return launch_paths_worklist<L.nreg_h, L.lpl_h, L.nreg_o, L.lpl_o>(wl, ndisp, u8, nblocks, stream);
+    return launch_paths_worklist<L.nreg_h, L.lpl_h, L.nreg_o, L.lpl_o>(wl, ndisp, p2, nblocks, stream);
 }
 #endif
 

@@ -50,6 +50,10 @@ __device__ __forceinline__ uint4 load_once16(const void* p) {
 // ---------------------------------------------------------------------------
 __host__ __device__ inline bool slices_u8(int p2) { return p2 <= 127; }
 
+// Largest P2 whose path states stay below 0x7C00 in every step (paths.hip): any
+// that 8 paths may have; with 4 paths P2 goes up to 16128.
+constexpr int kNarrowP2 = 7936;
+
 // Path sum of 16 consecutive volume elements (Eq. sgm_path_aggr) from NS
 // uint8 pair slices: S = MUL * C + sum of the slices, MUL = npaths.  Bytes
 // are split into even / odd 16-bit lanes, so plain 32-bit adds carry two
@@ -286,6 +290,8 @@ constexpr PathLayout kPathLayouts[kNumPathLayouts] = {
     {4, 16, 4, 16, true, false, false, 96, 132, 149},
     {4, 16, 4, 16, false, false, false, 124, 132, 147},
 };
+// Layouts that are also built for a P2 beyond kNarrowP2: one for every D.
+constexpr bool layout_wide(int id) { return id <= 5 || id == 7 || id == 12; }
 #define SGM_PATH_LAYOUT_IDS(X)                                                                      \
     X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)      \
     X(17) X(18) X(19) X(20) X(21) X(22) X(23) X(24) X(25)
@@ -294,15 +300,15 @@ constexpr PathLayout kPathLayouts[kNumPathLayouts] = {
 // in two objects): the single-frame kernel for one frame, or the work-list
 // kernel for a batch.
 template <int ID>
-hipError_t launch_paths_layout_id(const Frame& one, int ndisp, bool u8, int nblocks, hipStream_t stream);
+hipError_t launch_paths_layout_id(const Frame& one, int ndisp, int p2, int nblocks, hipStream_t stream);
 template <int ID>
-hipError_t launch_paths_batch_layout_id(const WorkList& wl, int ndisp, bool u8, int nblocks,
+hipError_t launch_paths_batch_layout_id(const WorkList& wl, int ndisp, int p2, int nblocks,
                                         hipStream_t stream);
 #define SGM_DECLARE_PATH_LAYOUT(K)                                                              \
     template <>                                                                                 \
-    hipError_t launch_paths_layout_id<K>(const Frame&, int, bool, int, hipStream_t);            \
+    hipError_t launch_paths_layout_id<K>(const Frame&, int, int, int, hipStream_t);             \
     template <>                                                                                 \
-    hipError_t launch_paths_batch_layout_id<K>(const WorkList&, int, bool, int, hipStream_t);
+    hipError_t launch_paths_batch_layout_id<K>(const WorkList&, int, int, int, hipStream_t);
 SGM_PATH_LAYOUT_IDS(SGM_DECLARE_PATH_LAYOUT)
 #undef SGM_DECLARE_PATH_LAYOUT
 
@@ -327,6 +333,8 @@ __host__ __device__ inline int pair_blocks(int q, int width, int height, const P
 }
 int path_variants(int ndisp);                       // number of variants (>= 1)
 int default_variant(int width, int height, int ndisp, int npaths);
+// the one variant with kernels for a P2 beyond kNarrowP2
+int wide_variant(int ndisp);
 // of several frames of one disparity range whose blocks share a launch
 struct FrameSize {
     int width, height;

@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 NDISP = [9, 13, 16, 17, 24, 32, 33, 40, 48, 50, 64, 65, 80, 100, 128, 129, 200, 208, 256]
 
 
-@pytest.mark.parametrize("p1,p2,npaths", [(10, 120, 8), (90, 880, 8), (10, 120, 4)])
+@pytest.mark.parametrize("p1,p2,npaths", [(10, 120, 8), (90, 880, 8), (10, 120, 4), (7936, 7936, 8),
+                                           (7937, 7937, 4)])
 @pytest.mark.parametrize("nd", NDISP)
 def test_every_variant_is_exact(nd, p1, p2, npaths):
     import torch
@@ -38,3 +39,26 @@ def test_every_variant_is_exact(nd, p1, p2, npaths):
             np.testing.assert_array_equal(plan.disp[i].cpu().numpy(), w["disp"], err_msg=f"{shapes[i]} variant {v}")
             np.testing.assert_array_equal(plan.disp_right[i].cpu().numpy(), w["disp_right"])
         plan.close()
+
+
+@pytest.mark.parametrize("p1,p2,npaths", [(127, 128, 8), (3000, 7936, 8), (7936, 7936, 8), (7936, 7936, 4), (1, 7937, 4),
+                                          (16128, 16128, 4)])
+@pytest.mark.parametrize("nd", [3, 13, 16, 30, 64, 100, 128, 200, 256])
+def test_large_penalties(nd, p1, p2, npaths):
+    """S_bar with path states as large as they get: costs of 255 over whole
+    lines, a few small ones, and P1 up to P2."""
+    import torch
+
+    import oracle
+    from paper_2106_07927_amd import sgm
+    for w, h in ((70, 40), (33, 50)):
+        print("penalties", nd, p1, p2, npaths, w, h, flush=True)
+        rng = np.random.Generator(np.random.PCG64(nd + w))
+        cost = np.full((h, w, nd), 255, np.uint8)
+        some = rng.random(cost.shape)
+        cost[some < 0.2] = rng.integers(0, 256, int((some < 0.2).sum()))
+        cost[:, : w // 2][some[:, : w // 2] >= 0.001] = 255
+        got = sgm.sgm_aggregate(torch.from_numpy(cost).cuda(), npaths, p1, p2)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(got.view(torch.int16).cpu().numpy().view(np.uint16),
+                                      oracle.aggregate(cost, npaths, p1, p2))

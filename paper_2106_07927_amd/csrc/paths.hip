@@ -121,6 +121,14 @@ __device__ __forceinline__ uint32_t pk_min3(uint32_t a, uint32_t b, uint32_t c) 
     }
 }
 
+// The smaller half of v in both halves (one instruction: the swap is an operand
+// modifier).
+__device__ __forceinline__ uint32_t pk_min_swapped(uint32_t v) {
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    const u16x2 x = __builtin_bit_cast(u16x2, v);
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(x, __builtin_shufflevector(x, x, 1, 0)));
+}
+
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp0(uint32_t v) {      // lanes without a source read 0
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
@@ -148,7 +156,7 @@ __device__ __forceinline__ uint32_t line_min2(const uint32_t (&L)[NREG]) {
     } else if constexpr (NREG == 2) {
         v = pk_min(v, L[1]);
     }
-    v = pk_min(v, __builtin_amdgcn_alignbit(v, v, 16));
+    v = pk_min_swapped(v);
     if constexpr (LPL >= 2) v = min(v, dpp0<kDppQuadSwap1>(v));
     if constexpr (LPL >= 4) v = min(v, dpp0<kDppQuadSwap2>(v));
     if constexpr (LPL >= 8) v = min(v, dpp0<kDppRowHalfMirror>(v));
@@ -181,6 +189,21 @@ __device__ __forceinline__ uint32_t lane_prev(uint32_t v) {
     else if constexpr (LPL <= 16) return dpp0<kDppRowShr1>(v);
     else return dpp0<0x138>(v);
 }
+
+// Where a line is a row of 16 lanes or the whole wave, its edge lanes have no
+// source: registers that a lane shift leaves alone there and that are kept from
+// step to step need their edge value only once.  (Not with 8 registers per
+// lane, where no more fit.)
+template <int NREG, int LPL>
+struct Beside {
+    static constexpr bool kKeeps = (LPL == 16 || LPL == 64) && NREG < 8;
+    uint32_t next, prev;
+    __device__ __forceinline__ void shift(uint32_t lowest, uint32_t highest) {
+        constexpr int kNext = LPL <= 16 ? kDppRowShl1 : 0x130, kPrev = LPL <= 16 ? kDppRowShr1 : 0x138;
+        next = (uint32_t)__builtin_amdgcn_update_dpp((int)next, (int)lowest, kNext, 0xF, 0xF, false);
+        prev = (uint32_t)__builtin_amdgcn_update_dpp((int)prev, (int)highest, kPrev, 0xF, 0xF, false);
+    }
+};
 
 // ---- bytes of one lane for one pixel: 2*NREG bytes --------------------------
 template <int NREG>
@@ -476,10 +499,17 @@ struct LaneConst {
 // the lane, from the state L and its line minimum m (m2: in both halves).
 template <int NREG, int LPL, bool NARROW, bool RAGGED>
 __device__ __forceinline__ void relax(const uint32_t (&L)[NREG], uint32_t m2, const LaneConst<NREG, RAGGED>& lc,
-                                      uint32_t (&V)[NREG]) {
+                                      Beside<NREG, LPL>& beside, uint32_t (&V)[NREG]) {
     const uint32_t cap = m2 + lc.p2x2;           // no carry crosses the halves
-    const uint32_t nx = lane_next<LPL>(L[0]) | lc.edge_next;
-    const uint32_t pv = lane_prev<LPL>(L[NREG - 1]) | lc.edge_prev;
+    uint32_t nx, pv;
+    if constexpr (Beside<NREG, LPL>::kKeeps) {
+        beside.shift(L[0], L[NREG - 1]);
+        nx = beside.next;
+        pv = beside.prev;
+    } else {
+        nx = lane_next<LPL>(L[0]) | lc.edge_next;
+        pv = lane_prev<LPL>(L[NREG - 1]) | lc.edge_prev;
+    }
     const uint32_t below = __builtin_amdgcn_alignbit(L[NREG - 1], pv, 16);    // of register 0
     const uint32_t above = __builtin_amdgcn_alignbit(nx, L[0], 16);           // of register NREG - 1
 #pragma unroll
@@ -634,6 +664,7 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
     constexpr uint32_t kEdge = NARROW ? 0x4000u : 0x8000u;
     cst.edge_next = sub == LPL - 1 ? kEdge : 0u;
     cst.edge_prev = sub == 0 ? kEdge << 16 : 0u;
+    Beside<NREG, LPL> beside = {cst.edge_next, cst.edge_prev};
     const uint32_t lift = 255u + (uint32_t)f.p2;
 #pragma unroll
     for (int k = 0; k < (RAGGED ? NREG : 1); ++k) {
@@ -724,7 +755,7 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
             for (int k = 0; k < NREG; ++k) L[k] -= m2;
             m2 = 0;
         }
-        relax<NREG, LPL, NARROW>(L, m2, cst, V);
+        relax<NREG, LPL, NARROW>(L, m2, cst, beside, V);
         advance<NREG, PADDED>(V, cost, cst, L);
         return m2;
     };
@@ -770,7 +801,7 @@ __device__ __forceinline__ void run_wave(const Frame& f, uint8_t* __restrict__ s
     auto partner_step = [&](int j, PartnerSteps& out, const ByteVec<NREG>& cost) {
         uint32_t V[NREG];
         const uint32_t m2 = line_min2<NREG, LPL, NARROW>(P);
-        relax<NREG, LPL, NARROW>(P, m2, cst, V);
+        relax<NREG, LPL, NARROW>(P, m2, cst, beside, V);
         advance<NREG, PADDED>(V, cost, cst, P);
         if constexpr (U8) {
             const uint32_t nm = neg257<NREG>(m2);

@@ -208,7 +208,7 @@ class Frame:
         second = self.npaths * self.des + 4 * self.w * self.h
         return {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                "kernel": "sgm_aggregate_select (paths_kernel + select_fused_kernel + "
+                "kernel": "sgm_aggregate_select (paths_kernel + select_tile_kernel + "
                           "check_median_kernel)",
                 "algorithmic_bytes": b, "t_agg_us": round(agg_ms * 1e3, 2),
                 "basis": "(R+2)*N*D: the cost volume streamed once per path plus S_bar written "

@@ -298,7 +298,8 @@ size_t sgm_batch_workspace_bytes(const sgm_pair* pairs, int32_t n,
  * with two kinds of entries:
  *   "WxHxD": n   the path-kernel lane-layout variant for pairs of that shape
  *                (other shapes use the library's default for their size, as
- *                the single-frame calls do);
+ *                the single-frame calls do; those below 100k pixels, which
+ *                share their launches, one default per ndisp);
  *   "chains": n  how many streams inside the graph the pairs of 100k pixels
  *                and more are spread over, 1..8 (default 2); pairs on
  *                different streams may overlap.

@@ -4,14 +4,14 @@
 // Plan creation lays every frame's intermediates out in the caller's
 // workspace, groups the frames by what the kernels are compiled for
 // (disparity range, and for the path pass the lane-layout variant chosen by
-// the tuning table), writes one device work list per stage and group, and
+// the tuning table or for all blocks of the range), writes one device work list per stage and group, and
 // captures the whole sequence into a hipGraph:
 //     census (all frames, both images) -> cost (per D) -> paths (per D and
 //     variant) -> D^R key fill (all) -> path sum fused with the selection
 //     (per D) -> LR check + median (all)
-// Every stage is one persistent launch that walks its work list of
-// (frame, block) items; the blocks of a frame are exactly those of the
-// single-frame call, so each frame's results are bit-identical to it.
+// Every stage is one launch over its work list of (frame, block) items; the
+// blocks of a frame are exactly those of the single-frame call, so each frame's
+// results are bit-identical to it.
 // Only frames below kSmallPixels go through these work lists: there a
 // stage's blocks of many frames fill the GPU where one frame's would not.
 // A larger frame already fills it and runs faster through the single-frame

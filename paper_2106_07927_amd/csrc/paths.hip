@@ -34,11 +34,13 @@
 // volume is read once per direction.  The pass is bound by that traffic on
 // all but small frames (per volume element 8 + 4 + 1 bytes for 8 paths, where
 // storing the first half's values instead took 8 + 8 + 4); the steps walked
-// twice cost less than the bytes they save: 1920x1080, D = 256: 1910 -> 1114
-// us, 1242x375, D = 128: 182 -> 135 us, with P2 = 880: 320 -> 207 us.
+// twice cost less than the bytes they save: 1920x1080, D = 256: 1910 -> 1102
+// us (6.2 TB/s), 1242x375, D = 128: 182 -> 134 us, with P2 = 880: 320 -> 203 us.
 // In small frames a line is a chain that nothing else hides.  There two more
 // waves per line group (PathLayout::help_*) walk the partner's steps and hand
-// them over through LDS, a chunk ahead: 320x240, D = 64, 4 paths: 30 -> 24 us.
+// them over through LDS, a chunk ahead: 320x240, D = 64, 4 paths: 30 -> 24 us
+// (67 ns a step: some 32 instructions, which one wave issues at best every two
+// nanoseconds).
 // Where lines are many the same waves do better on lines of their own.
 //
 // Both waves run the same number of steps T = n + delta (a multiple of K):
@@ -1044,7 +1046,7 @@ __global__ __launch_bounds__(kThreads, 2) void paths_batch_kernel(WorkList wl) {
 }
 
 // Path-kernel launches for one lane layout: the single-frame kernel, or the
-// persistent work-list form.  The two are compiled in separate objects
+// work-list form.  The two are compiled in separate objects
 // (SGM_PATH_PART 0 and 1), so the library's longest compile splits in two.
 struct LayoutFlags {
     bool ragged, padded;   // D cuts a lane's disparities; some lane holds padding

@@ -47,12 +47,14 @@ __device__ __forceinline__ float refine(int d, uint32_t s_prev, uint32_t s_min, 
 //      disparities.  Each pixel every T moves on by one disparity (one lane
 //      shift) and takes in the pixel's key; what leaves at d = D - 1 is the
 //      segment's minimum for q = x - D + 1.  The segments meet in LDS, then
-//      one atomicMin per q merges the tile into the D^R key map.
+//      one atomicMin per q merges the tile into the D^R key map.  Up to 32
+//      disparities a wave walks two or four segments at once, GL lanes each
+//      (selection from S_bar, 640x480, D = 16: 10.9 us with one, now 6.8).
 // Keys are built with one byte permute per value (the disparity bytes of a
 // lane are constants).  The fused form is bound by the bytes it reads (NS + 1
-// per element: 49 us at 1242x375, D = 128, 6.1 TB/s); the pass over S_bar was
+// per element: 46 us at 1242x375, D = 128, 6.5 TB/s); the pass over S_bar was
 // bound by its instructions (17 per element, D^R folded by one thread per q:
-// 33 us) before (2) and (3) took this form.
+// 33 us) before (2) and (3) took this form, 25 us since.
 // NS pair slices: uint8 (S_bar = 2 NS C + sum) or uint16 (S_bar = sum).
 struct TileShape {
     int rs, tpx, width, ndisp, x0, npx;
@@ -172,7 +174,7 @@ __device__ __forceinline__ uint32_t key_hi(uint32_t w, uint32_t ds, int e) {
     return __builtin_amdgcn_perm(w, ds, 0x0c070600u | (uint32_t)e);
 }
 
-template <int EPL, bool FLAT, int NS, bool U8, bool FINE>
+template <int EPL, int GL, bool FLAT, int NS, bool U8, bool FINE>
 __device__ __forceinline__ void select_tile_block(uint16_t* __restrict__ sb, const Frame& f, int bx,
                                                   int y) {
     const TileShape t(f, bx, y, FLAT);
@@ -226,7 +228,36 @@ __device__ __forceinline__ void select_tile_block(uint16_t* __restrict__ sb, con
     }
 
     // (3) D^R
-    {
+    if constexpr (GL < 64) {
+        constexpr int kSeg = kFusedTile / (4 * (64 / GL));       // pixels per group of lanes
+        const int d = threadIdx.x % GL;
+        const int s0 = (int)threadIdx.x / GL * kSeg, s1 = min(npx, s0 + kSeg);
+        const uint32_t off = d < ndisp ? 0u : kInf;
+        const uint16_t* src = sb + first + s0 * t.rs + d;
+        uint32_t T = kInf, exits[kSeg];                          // exits: of the lane d = D - 1
+#pragma unroll
+        for (int i = 0; i < kSeg; ++i) {
+            const uint32_t key = ((uint32_t)src[i * t.rs] << 8) | (uint32_t)d | off;
+            uint32_t carry;
+            if constexpr (GL == 16) {
+                carry = dpp<kDppRowShr1>(kInf, T);
+            } else {
+                carry = (uint32_t)__builtin_amdgcn_update_dpp((int)kInf, (int)T, 0x138, 0xF, 0xF, false);
+                carry = d == 0 ? kInf : carry;
+            }
+            T = s0 + i < s1 ? min(carry, key) : T;
+            exits[i] = T;
+        }
+        if (s0 < s1) {
+            if (d == ndisp - 1) {
+#pragma unroll
+                for (int i = 0; i < kSeg; ++i)
+                    if (s0 + i < s1) atomicMin(&rk[s0 + i], exits[i]);
+            } else if (d < ndisp) {
+                atomicMin(&rk[s1 - 1 - d + ndisp - 1], T);
+            }
+        }
+    } else {
         const int lane = threadIdx.x & 63;
         const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
         constexpr int kSeg = EPL == 4 ? 8 : 16;    // pixels per wave
@@ -289,13 +320,13 @@ __device__ __forceinline__ void select_tile_block(uint16_t* __restrict__ sb, con
     __syncthreads();   // the LDS tile is reused by the next work item
 }
 
-template <int EPL, bool FLAT, int NS, bool U8, bool FINE>
+template <int EPL, int GL, bool FLAT, int NS, bool U8, bool FINE>
 __global__ __launch_bounds__(256) void select_tile_kernel(Frame f) {
     extern __shared__ __align__(16) uint16_t sb[];
-    select_tile_block<EPL, FLAT, NS, U8, FINE>(sb, f, blockIdx.x, blockIdx.y);
+    select_tile_block<EPL, GL, FLAT, NS, U8, FINE>(sb, f, blockIdx.x, blockIdx.y);
 }
 
-template <int EPL, bool FLAT, int NS, bool U8>
+template <int EPL, int GL, bool FLAT, int NS, bool U8>
 __global__ __launch_bounds__(256) void select_tile_batch_kernel(WorkList wl) {
     extern __shared__ __align__(16) uint16_t sb[];
     for (int b = blockIdx.x; b < wl.total; b += gridDim.x) {
@@ -303,7 +334,7 @@ __global__ __launch_bounds__(256) void select_tile_batch_kernel(WorkList wl) {
         const Frame& f = wl.frames[fi];
         const int lb = b - wl.starts[fi];
         const int bxs = fused_blocks_x(f.width, f.ndisp);
-        select_tile_block<EPL, FLAT, NS, U8, false>(sb, f, lb % bxs, lb / bxs);
+        select_tile_block<EPL, GL, FLAT, NS, U8, false>(sb, f, lb % bxs, lb / bxs);
     }
 }
 
@@ -450,26 +481,28 @@ __global__ __launch_bounds__(256) void flip_pair_kernel(const uint8_t* __restric
     mat[dst] = left[src];
 }
 
-template <int EPL, bool FLAT, int NS, bool U8, bool FINE>
+template <int EPL, int GL, bool FLAT, int NS, bool U8, bool FINE>
 void launch_tile_kernel(const Frame* one, const WorkList* wl, int ndisp, hipStream_t stream) {
     const size_t lds = tile_lds_bytes(ndisp);
     if (one) {
         const dim3 g(fused_blocks_x(one->width, ndisp), one->height);
-        select_tile_kernel<EPL, FLAT, NS, U8, FINE><<<g, 256, lds, stream>>>(*one);
+        select_tile_kernel<EPL, GL, FLAT, NS, U8, FINE><<<g, 256, lds, stream>>>(*one);
     } else if constexpr (NS > 1 && !FINE) {
-        select_tile_batch_kernel<EPL, FLAT, NS, U8><<<persistent_grid(wl->total), 256, lds, stream>>>(*wl);
+        select_tile_batch_kernel<EPL, GL, FLAT, NS, U8><<<persistent_grid(wl->total), 256, lds, stream>>>(*wl);
     }
 }
 
 // frames of one launch share D
 template <int NS, bool U8, bool FINE>
 void launch_tile(const Frame* one, const WorkList* wl, int ndisp, hipStream_t stream) {
-#define SGM_TILE(E)                                                                            \
-    (ndisp % 16 == 0 ? launch_tile_kernel<E, false, NS, U8, FINE>(one, wl, ndisp, stream)      \
-                     : launch_tile_kernel<E, true, NS, U8, FINE>(one, wl, ndisp, stream))
-    if (ndisp <= 64) SGM_TILE(1);
-    else if (ndisp <= 128) SGM_TILE(2);
-    else SGM_TILE(4);
+#define SGM_TILE(E, G)                                                                         \
+    (ndisp % 16 == 0 ? launch_tile_kernel<E, G, false, NS, U8, FINE>(one, wl, ndisp, stream)   \
+                     : launch_tile_kernel<E, G, true, NS, U8, FINE>(one, wl, ndisp, stream))
+    if (ndisp <= 16) SGM_TILE(1, 16);
+    else if (ndisp <= 32) SGM_TILE(1, 32);
+    else if (ndisp <= 64) SGM_TILE(1, 64);
+    else if (ndisp <= 128) SGM_TILE(2, 64);
+    else SGM_TILE(4, 64);
 #undef SGM_TILE
 }
 

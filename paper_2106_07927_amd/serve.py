@@ -158,7 +158,7 @@ def slot_bytes(spec: StreamSpec, npaths: int, p2: int) -> int:
     """Device bytes of one slot as the arena carves it, each buffer rounded up
     to 256 bytes: the two input images, both census maps, the cost volume,
     the two disparity maps, and the workspace of the streamlined aggregation
-    (path slices, S_bar only where the fused selection does not apply, D^R
+    (path slices, room for S_bar where D is no multiple of 16, D^R
     keys, D^L); one path slice per pair of opposite directions, uint8 for
     P2 <= 127, else uint16."""
     n = spec.width * spec.height

@@ -12,7 +12,7 @@ from paper_2106_07927_amd import datagen
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("nd", [1, 2, 7, 15, 16, 17, 31, 48, 63, 64, 65, 80, 100, 101, 127, 128, 129, 144, 200,
+@pytest.mark.parametrize("nd", [1, 2, 3, 7, 15, 16, 17, 31, 32, 48, 63, 64, 65, 80, 100, 101, 127, 128, 129, 144, 200,
                                 203, 255, 256])
 def test_selection_at_tile_edges(nd):
     import torch

@@ -30,7 +30,7 @@ __device__ __forceinline__ float refine(int d, uint32_t s_prev, uint32_t s_min, 
 // ---- the tile pass -----------------------------------------------------------
 // A block owns a tile of one row: 64 pixels, or 32 when D > 128, so that the
 // tile holds at most 8192 volume elements.
-//  (1) Its 256 threads read blocks of 16 elements from every pair slice (and,
+//  (1) Its 256 threads read blocks of 16 bytes from every pair slice (and,
 //      for uint8 slices, from the cost volume) -- all loads issued before any
 //      is used -- and sum them into an LDS copy of S_bar, so that in the
 //      streamlined form S_bar never goes to HBM.  Without FLAT (D % 16 == 0)
@@ -90,23 +90,27 @@ __device__ __forceinline__ uint4 load16_checked(const uint8_t* __restrict__ p, s
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// (1): returns the LDS index of the tile's first value
+// (1): returns the LDS index of the tile's first value.  A thread's blocks are
+// 16 bytes of a slice, so the lanes of a load read on end: 16 elements of uint8
+// slices, 8 of uint16 ones (two loads of 32 bytes a lane: 97 us at 1242x375,
+// D = 128, P2 = 880; now 77).
 template <bool FLAT, int NS, bool U8>
 __device__ __forceinline__ int tile_sum(uint16_t* __restrict__ sb, const Frame& f, const TileShape& t) {
+    constexpr int B = U8 ? 16 : 8;                 // elements of a block
     const int ndisp = t.ndisp;
     const uint32_t e_tile = (uint32_t)(t.row + t.x0) * (uint32_t)ndisp;
     const uint32_t e_end = (uint32_t)(t.row + t.x0 + t.npx) * (uint32_t)ndisp;
     const size_t n = (size_t)f.width * f.height * ndisp;
-    const uint32_t e0 = FLAT ? e_tile & ~15u : e_tile;
-    const int nblk = FLAT ? (int)((e_end - e0 + 15u) >> 4) : (t.tpx * ndisp) >> 4;
+    const uint32_t e0 = FLAT ? e_tile & ~(uint32_t)(B - 1) : e_tile;
+    const int nblk = FLAT ? (int)((e_end - e0 + (uint32_t)(B - 1)) / B) : t.tpx * ndisp / B;
     // blocks past the tile's end re-read its last block and land in LDS that is
     // never read
-    const uint32_t e_last = FLAT ? (e_end - 1u) & ~15u : e_end - 16u;
-    // b / (blocks per row) by a product: exact for b < 512
-    const uint32_t bpr = (uint32_t)ndisp >> 4;
+    const uint32_t e_last = FLAT ? (e_end - 1u) & ~(uint32_t)(B - 1) : e_end - (uint32_t)B;
+    // b / (blocks per row) by a product: exact for b < 1024 and at most 32 of them
+    const uint32_t bpr = (uint32_t)ndisp / B;
     const uint32_t magic = FLAT ? 0u : (65536u + bpr - 1u) / bpr;
-    constexpr int kPasses = FLAT ? 3 : 2;          // a FLAT tile has up to 514 blocks
-    uint32_t sum[kPasses][8];
+    constexpr int kPasses = (U8 ? 2 : 4) + (FLAT ? 1 : 0);     // a FLAT tile has up to two blocks more
+    uint32_t sum[kPasses][B / 2];
     if constexpr (U8) {
         uint4 c[kPasses];
         uint4 a[kPasses][NS];
@@ -125,42 +129,45 @@ __device__ __forceinline__ int tile_sum(uint16_t* __restrict__ sb, const Frame& 
         }
     } else {
         const uint16_t* slices = reinterpret_cast<const uint16_t*>(f.slices);
-        uint4 a[kPasses][NS][2];
+        uint4 a[kPasses][NS];
 #pragma unroll
         for (int i = 0; i < kPasses; ++i) {
             if (256 * i >= nblk) break;
-            const uint32_t e = min(e0 + 16u * (uint32_t)(threadIdx.x + 256 * i), e_last);
+            const uint32_t e = min(e0 + 8u * (uint32_t)(threadIdx.x + 256 * i), e_last);
 #pragma unroll
             for (int r = 0; r < NS; ++r) {
                 // NS == 1: the caller's S_bar, which ends with its last value
-                if (FLAT && NS == 1 && e + 16u > n) {
-                    const uint8_t* b = reinterpret_cast<const uint8_t*>(slices);
-                    a[i][r][0] = load16_checked(b, 2 * (size_t)e, 2 * n);
-                    a[i][r][1] = load16_checked(b, 2 * (size_t)e + 16, 2 * n);
-                } else {
-                    a[i][r][0] = load_once16(slices + (size_t)r * f.slice_stride + e);
-                    a[i][r][1] = load_once16(slices + (size_t)r * f.slice_stride + e + 8);
-                }
+                if (FLAT && NS == 1 && e + 8u > n)
+                    a[i][r] = load16_checked(reinterpret_cast<const uint8_t*>(slices), 2 * (size_t)e, 2 * n);
+                else a[i][r] = load_once16(slices + (size_t)r * f.slice_stride + e);
             }
         }
 #pragma unroll
         for (int i = 0; i < kPasses; ++i) {
             if (256 * i >= nblk) break;
-            wide_sum16<NS>(a[i], sum[i]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) sum[i][k] = 0;
+#pragma unroll
+            for (int r = 0; r < NS; ++r) {         // S_bar fits 16 bits: no carry crosses the halves
+                sum[i][0] += a[i][r].x;
+                sum[i][1] += a[i][r].y;
+                sum[i][2] += a[i][r].z;
+                sum[i][3] += a[i][r].w;
+            }
         }
     }
 #pragma unroll
     for (int i = 0; i < kPasses; ++i) {
         const int b = threadIdx.x + 256 * i;
         if (b < nblk) {
-            int at = 16 * b;
+            int at = B * b;
             if constexpr (!FLAT) {
                 const int p = (int)(((uint32_t)b * magic) >> 16);
-                at = p * t.rs + 16 * (b - p * (int)bpr);
+                at = p * t.rs + B * (b - p * (int)bpr);
             }
             uint4* dst = reinterpret_cast<uint4*>(sb + at);
             dst[0] = make_uint4(sum[i][0], sum[i][1], sum[i][2], sum[i][3]);
-            dst[1] = make_uint4(sum[i][4], sum[i][5], sum[i][6], sum[i][7]);
+            if constexpr (U8) dst[1] = make_uint4(sum[i][4], sum[i][5], sum[i][6], sum[i][7]);
         }
     }
     return (int)(e_tile - e0);

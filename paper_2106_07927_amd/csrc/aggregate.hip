@@ -211,11 +211,18 @@ int default_variant(const FrameSize* sizes, int n, int ndisp, int npaths) {
     return fastest_variant(sizes, n, ndisp, npaths, runs.data());
 }
 
-int default_variant(int width, int height, int ndisp, int npaths) {
-    // 8 paths of the widest ranges are bound by memory, where helpers read the
-    // cost bytes of the horizontal lines once more than they save in wide
-    // frames (1242x375, D = 256: 281 us with them, 254 without)
-    if (ndisp > 128 && ndisp % 16 == 0 && npaths == 8 && width > 2 * height && (long)width * height >= 400000) return 1;
+int default_variant(int width, int height, int ndisp, int npaths, int p2) {
+    // 8 paths of the widest ranges are bound by memory.  In wide frames helpers
+    // cost more there, reading the cost bytes of the horizontal lines once more,
+    // than they save (1242x375, D = 256: 281 us with them, 254 without)
+    const long px = (long)width * height;
+    if (ndisp > 128 && ndisp % 16 == 0 && npaths == 8) {
+        // uint16 slices of the largest frames: eight disparities per lane, one
+        // 16-byte store each, streamed to memory without half-written pieces
+        // (1920x1080, D = 256: 1689 us, 1921 with sixteen; 1280x720 818 and 787)
+        if (!slices_u8(p2) && px >= 1500000) return 2;
+        if (width > 2 * height && px >= 400000) return 1;
+    }
     const FrameSize size = {width, height};
     Run runs[4];
     return fastest_variant(&size, 1, ndisp, npaths, runs);
@@ -261,7 +268,7 @@ hipError_t launch_paths(const Frame& f, hipStream_t stream) {
     const int variant = f.p2 > kNarrowP2 ? wide_variant(f.ndisp)
                         : (f.variant >= 0 && f.variant < path_variants(f.ndisp))
                             ? f.variant
-                            : default_variant(f.width, f.height, f.ndisp, f.npaths);
+                            : default_variant(f.width, f.height, f.ndisp, f.npaths, f.p2);
     const int nb = path_blocks(f.width, f.height, f.ndisp, f.npaths, variant);
     return launch_paths_any(&f, nullptr, f.ndisp, variant, f.p2, nb, stream);
 }

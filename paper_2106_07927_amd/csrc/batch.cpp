@@ -173,7 +173,7 @@ size_t build_layout(const sgm_pair* pairs, int32_t n, const sgm_params* p, const
                                       : (tv >= 0 && tv < path_variants(q.ndisp)) ? tv : -1;
         if (f.variant < 0) {
             if (small_frame(f)) untuned[q.ndisp].push_back(i);
-            else f.variant = default_variant(q.width, q.height, q.ndisp, p->npaths);
+            else f.variant = default_variant(q.width, q.height, q.ndisp, p->npaths, p->p2);
         }
         f.left = q.left;
         f.right = q.right;

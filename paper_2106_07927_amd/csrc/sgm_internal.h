@@ -332,7 +332,7 @@ __host__ __device__ inline int pair_blocks(int q, int width, int height, const P
     return (pair_lines(q, width, height) + lpb - 1) / lpb;
 }
 int path_variants(int ndisp);                       // number of variants (>= 1)
-int default_variant(int width, int height, int ndisp, int npaths);
+int default_variant(int width, int height, int ndisp, int npaths, int p2);
 // the one variant with kernels for a P2 beyond kNarrowP2
 int wide_variant(int ndisp);
 // of several frames of one disparity range whose blocks share a launch

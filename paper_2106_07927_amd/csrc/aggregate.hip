@@ -138,28 +138,44 @@ struct Run {
 // blocks that share one cost the longest's time plus half of the others'.
 // Against timed passes of 16 .. 256 disparities, 4 and 8 paths, 160x120 ..
 // 1920x1080: off by 5% in the mean while memory does not bound the pass.
+// A batch plan may reckon thousands of runs, so each is dealt once: its whole
+// rounds over the units as one sum, the rest block by block (4,000 pairs of one
+// size: 1 ms, all of different sizes: 10 ms; holding every run against every
+// other took 660 ms and more).
 float run_time(const Run* runs, int n) {
     constexpr int kUnits = 256;
     constexpr float kShared = 0.5f;
-    float worst = 0.0f;
-    // what a unit holds changes only where a run begins
-    for (int k = 0, first = 0; k < n; first += runs[k++].blocks) {
-        float sum = 0.0f, longest = 0.0f;
-        int b = first % kUnits;
-        for (int at = 0, start = 0; at < n; start += runs[at++].blocks) {
-            for (; b < start + runs[at].blocks; b += kUnits) {
-                sum += runs[at].us;
-                longest = std::max(longest, runs[at].us);
-            }
+    float sum[kUnits] = {}, longest[kUnits] = {};
+    float every_sum = 0.0f, every_longest = 0.0f;      // of the whole rounds, on every unit
+    int unit = 0;
+    for (int k = 0; k < n; ++k) {
+        const int rounds = runs[k].blocks / kUnits;
+        if (rounds > 0) {
+            every_sum += (float)rounds * runs[k].us;
+            every_longest = std::max(every_longest, runs[k].us);
         }
-        worst = std::max(worst, longest + kShared * (sum - longest));
+        for (int b = runs[k].blocks % kUnits; b > 0; --b) {
+            sum[unit] += runs[k].us;
+            longest[unit] = std::max(longest[unit], runs[k].us);
+            unit = (unit + 1) % kUnits;
+        }
+    }
+    float worst = 0.0f;
+    for (int u = 0; u < kUnits; ++u) {
+        const float most = std::max(longest[u], every_longest);
+        worst = std::max(worst, most + kShared * (sum[u] + every_sum - most));
     }
     return worst;
 }
 
+// `count` frames of one size.
+struct Frames {
+    int width, height, count;
+};
+
 // The variant that run_time puts first; `runs` has room for npaths / 2 of them
-// per frame.
-int fastest_variant(const FrameSize* sizes, int n, int ndisp, int npaths, Run* runs) {
+// per size.
+int fastest_variant(const Frames* sizes, int n, int ndisp, int npaths, Run* runs) {
     const LayoutClass& c = layout_class(ndisp);
     if (c.n == 1) return 0;
     int best = -1;
@@ -171,10 +187,11 @@ int fastest_variant(const FrameSize* sizes, int n, int ndisp, int npaths, Run* r
         for (int i = 0; i < n; ++i) {
             const int w = sizes[i].width, h = sizes[i].height;
             for (int q = 0; q < npaths / 2; ++q)
-                runs[m++] = {pair_blocks(q, w, h, l), 1e-3f * (q == 0 ? w * l.ns_h : h * (q == 1 ? l.ns_v : l.ns_d))};
+                runs[m++] = {sizes[i].count * pair_blocks(q, w, h, l),
+                             1e-3f * (q == 0 ? w * l.ns_h : h * (q == 1 ? l.ns_v : l.ns_d))};
         }
         // work lists start with the longest lines
-        if (n > 1) std::sort(runs, runs + m, [](const Run& a, const Run& b) { return a.us > b.us; });
+        if (n > 1 || sizes[0].count > 1) std::sort(runs, runs + m, [](const Run& a, const Run& b) { return a.us > b.us; });
         const float us = run_time(runs, m);
         // up to D = 128 the first variant stays unless another is clearly
         // ahead: in wide frames it does better than reckoned (1242x375,
@@ -207,8 +224,18 @@ PathLayout path_layout(int ndisp, int variant) { return kPathLayouts[path_layout
 // 4 paths 91 -> 67; 1024x768, D = 128, 8 paths 270 -> 227; 320x240, D = 256,
 // 4 paths 49 -> 39; over 86 such sizes 13% less in the geometric mean.
 int default_variant(const FrameSize* sizes, int n, int ndisp, int npaths) {
-    std::vector<Run> runs((size_t)n * (npaths / 2));
-    return fastest_variant(sizes, n, ndisp, npaths, runs.data());
+    // a batch has many frames of few sizes
+    std::vector<FrameSize> sorted(sizes, sizes + n);
+    std::sort(sorted.begin(), sorted.end(), [](const FrameSize& a, const FrameSize& b) {
+        return a.width != b.width ? a.width < b.width : a.height < b.height;
+    });
+    std::vector<Frames> frames;
+    for (const FrameSize& s : sorted) {
+        if (!frames.empty() && frames.back().width == s.width && frames.back().height == s.height) ++frames.back().count;
+        else frames.push_back({s.width, s.height, 1});
+    }
+    std::vector<Run> runs(frames.size() * (size_t)(npaths / 2));
+    return fastest_variant(frames.data(), (int)frames.size(), ndisp, npaths, runs.data());
 }
 
 int default_variant(int width, int height, int ndisp, int npaths, int p2) {
@@ -223,7 +250,7 @@ int default_variant(int width, int height, int ndisp, int npaths, int p2) {
         if (!slices_u8(p2) && px >= 1500000) return 2;
         if (width > 2 * height && px >= 400000) return 1;
     }
-    const FrameSize size = {width, height};
+    const Frames size = {width, height, 1};
     Run runs[4];
     return fastest_variant(&size, 1, ndisp, npaths, runs);
 }

@@ -208,13 +208,6 @@ int fastest_variant(const Frames* sizes, int n, int ndisp, int npaths, Run* runs
 
 int path_variants(int ndisp) { return layout_class(ndisp).n; }
 
-int wide_variant(int ndisp) {
-    const LayoutClass& c = layout_class(ndisp);
-    int v = 0;
-    while (!layout_wide(c.id[v])) ++v;              // every range has one, and it takes every D
-    return v;
-}
-
 PathLayout path_layout(int ndisp, int variant) { return kPathLayouts[path_layout_id(ndisp, variant)]; }
 
 // Variant used when none is asked for (variant < 0): the one that run_time
@@ -292,8 +285,7 @@ size_t aggregate_work_bytes(int width, int height, int ndisp, int npaths, int p2
 }
 
 hipError_t launch_paths(const Frame& f, hipStream_t stream) {
-    const int variant = f.p2 > kNarrowP2 ? wide_variant(f.ndisp)
-                        : (f.variant >= 0 && f.variant < path_variants(f.ndisp))
+    const int variant = (f.variant >= 0 && f.variant < path_variants(f.ndisp))
                             ? f.variant
                             : default_variant(f.width, f.height, f.ndisp, f.npaths, f.p2);
     const int nb = path_blocks(f.width, f.height, f.ndisp, f.npaths, variant);

@@ -169,8 +169,7 @@ size_t build_layout(const sgm_pair* pairs, int32_t n, const sgm_params* p, const
         f.lr_tolerance = p->lr_tolerance;
         f.median3x3 = p->median3x3;
         const int tv = tuned_variant(tune_table, q.width, q.height, q.ndisp);
-        f.variant = p->p2 > kNarrowP2 ? wide_variant(q.ndisp)
-                                      : (tv >= 0 && tv < path_variants(q.ndisp)) ? tv : -1;
+        f.variant = (tv >= 0 && tv < path_variants(q.ndisp)) ? tv : -1;
         if (f.variant < 0) {
             if (small_frame(f)) untuned[q.ndisp].push_back(i);
             else f.variant = default_variant(q.width, q.height, q.ndisp, p->npaths, p->p2);

@@ -1060,16 +1060,13 @@ __host__ inline LayoutFlags layout_flags(int nh, int lh, int no, int lo, int ndi
 template <int NH, int LH, int NO, int LO>
 hipError_t launch_paths_single(const Frame& one, int ndisp, int p2, int nblocks, hipStream_t stream) {
     const LayoutFlags fl = layout_flags(NH, LH, NO, LO, ndisp);
-    constexpr bool kWide = layout_wide(SGM_PATH_LAYOUT);
 #define SGM_PATHS(A, B)                                                                                    \
     do {                                                                                                   \
         if (slices_u8(p2)) paths_kernel<NH, LH, NO, LO, A, B, A, B, true, true><<<nblocks, kThreads, 0, stream>>>(one);   \
         else if (p2 <= kNarrowP2)                                                                          \
             paths_kernel<NH, LH, NO, LO, A, B, A, B, false, true><<<nblocks, kThreads, 0, stream>>>(one);            \
-        else if constexpr (kWide)                                                                          \
-            paths_kernel<NH, LH, NO, LO, A, B, A, B, false, false><<<nblocks, kThreads, 0, stream>>>(one);           \
         else                                                                                               \
-            return hipErrorInvalidValue;                 /* wide_variant gives no other layout such a P2 */ \
+            paths_kernel<NH, LH, NO, LO, A, B, A, B, false, false><<<nblocks, kThreads, 0, stream>>>(one);           \
     } while (0)
     if (fl.ragged) {
         if constexpr (NO <= 4) SGM_PATHS(true, true);
@@ -1086,16 +1083,13 @@ hipError_t launch_paths_single(const Frame& one, int ndisp, int p2, int nblocks,
 template <int NH, int LH, int NO, int LO>
 hipError_t launch_paths_worklist(const WorkList& wl, int ndisp, int p2, int nblocks, hipStream_t stream) {
     const LayoutFlags fl = layout_flags(NH, LH, NO, LO, ndisp);
-    constexpr bool kWide = layout_wide(SGM_PATH_LAYOUT);
 #define SGM_PATHS(A, B)                                                                                    \
     do {                                                                                                   \
         if (slices_u8(p2)) paths_batch_kernel<NH, LH, NO, LO, A, B, A, B, true, true><<<nblocks, kThreads, 0, stream>>>(wl);   \
         else if (p2 <= kNarrowP2)                                                                          \
             paths_batch_kernel<NH, LH, NO, LO, A, B, A, B, false, true><<<nblocks, kThreads, 0, stream>>>(wl);            \
-        else if constexpr (kWide)                                                                          \
-            paths_batch_kernel<NH, LH, NO, LO, A, B, A, B, false, false><<<nblocks, kThreads, 0, stream>>>(wl);           \
         else                                                                                               \
-            return hipErrorInvalidValue;                 /* wide_variant gives no other layout such a P2 */ \
+            paths_batch_kernel<NH, LH, NO, LO, A, B, A, B, false, false><<<nblocks, kThreads, 0, stream>>>(wl);           \
     } while (0)
     if (fl.ragged) {
         if constexpr (NO <= 4) SGM_PATHS(true, true);

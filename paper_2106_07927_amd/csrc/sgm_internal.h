@@ -260,7 +260,8 @@ struct PathLayout {
     int ns_h, ns_v, ns_d;
 };
 
-// Every layout the library builds (paths.hip is compiled once per entry).
+// Every layout the library builds (paths.hip is compiled once per entry), each
+// for every P2.
 constexpr int kNumPathLayouts = 26;
 constexpr PathLayout kPathLayouts[kNumPathLayouts] = {
     {1, 1, 1, 1, true, false, false, 0, 0, 0},
@@ -290,8 +291,6 @@ constexpr PathLayout kPathLayouts[kNumPathLayouts] = {
     {4, 16, 4, 16, true, false, false, 96, 132, 149},
     {4, 16, 4, 16, false, false, false, 124, 132, 147},
 };
-// Layouts that are also built for a P2 beyond kNarrowP2: one for every D.
-constexpr bool layout_wide(int id) { return id <= 5 || id == 7 || id == 12; }
 #define SGM_PATH_LAYOUT_IDS(X)                                                                      \
     X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)      \
     X(17) X(18) X(19) X(20) X(21) X(22) X(23) X(24) X(25)
@@ -333,8 +332,6 @@ __host__ __device__ inline int pair_blocks(int q, int width, int height, const P
 }
 int path_variants(int ndisp);                       // number of variants (>= 1)
 int default_variant(int width, int height, int ndisp, int npaths, int p2);
-// the one variant with kernels for a P2 beyond kNarrowP2
-int wide_variant(int ndisp);
 // of several frames of one disparity range whose blocks share a launch
 struct FrameSize {
     int width, height;

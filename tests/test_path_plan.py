@@ -39,3 +39,46 @@ def test_planning_time_grows_with_the_number_of_pairs(lib):
     """16 times the pairs take about 16 times as long (sorting adds little); a
     choice that looks at every pair for every pair would take 256 times."""
     assert workspace_seconds(lib, 4800) < 64 * max(workspace_seconds(lib, 300), 1e-4)
+
+
+@pytest.mark.parametrize("p2", [120, 880, 7936, 7937, 16128])
+def test_a_tuned_variant_holds_for_every_penalty(lib, p2):
+    """Small frames of one D share the path launch of their variant; a table
+    that names two variants makes two launches, whose tables take room."""
+    prm = sgm.SgmParams(9, 7, 4, 7, p2, 1, 1)
+    pairs = (sgm.SgmPair * 2)()
+    for i, (w, h) in enumerate(((64, 48), (90, 33))):
+        pairs[i] = sgm.SgmPair(FAKE, FAKE, w, h, w, 100, FAKE, None)
+    room = lambda a, b: lib.sgm_batch_workspace_bytes(                                   # noqa: E731
+        pairs, 2, ctypes.byref(prm), b'{"64x48x100": %d, "90x33x100": %d}' % (a, b))
+    assert room(0, 3) > room(0, 0) > 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nd", [9, 16, 17, 32, 40, 64, 65, 128, 200, 256])
+def test_every_variant_with_the_largest_penalties(nd):
+    """P1 = P2 = 16128, 4 paths: path states as large as they get, in every
+    layout; frames narrower than D, so that many costs are 255."""
+    import json
+
+    import numpy as np
+    import torch
+
+    import oracle
+    from paper_2106_07927_amd import datagen
+    kw = dict(win_w=9, win_h=7, npaths=4, p1=16128, p2=16128, lr_tolerance=-1, median3x3=False)
+    shapes = [(57, 37), (21, 50)]
+    pairs = [datagen.random_images(w, h, 3 * nd + i) for i, (w, h) in enumerate(shapes)]
+    want = [oracle.run(a, b, oracle.Params(ndisp=nd, **kw)) for a, b in pairs]
+    lefts = [torch.from_numpy(a).cuda() for a, _ in pairs]
+    rights = [torch.from_numpy(b).cuda() for _, b in pairs]
+    for v in range(sgm.load_library().sgm_aggregate_variants(nd)):
+        print("largest penalties", nd, v, flush=True)
+        plan = sgm.BatchPlan(lefts, rights, [nd] * 2, sgm.Params(ndisp=0, **kw), want_right=True,
+                             tune_table=json.dumps({f"{w}x{h}x{nd}": v for w, h in shapes}))
+        plan.run()
+        torch.cuda.synchronize()
+        for i, o in enumerate(want):
+            np.testing.assert_array_equal(plan.disp[i].cpu().numpy(), o["disp"], err_msg=f"{shapes[i]} variant {v}")
+            np.testing.assert_array_equal(plan.disp_right[i].cpu().numpy(), o["disp_right"])
+        plan.close()

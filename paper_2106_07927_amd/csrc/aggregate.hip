@@ -237,10 +237,13 @@ int default_variant(int width, int height, int ndisp, int npaths, int p2) {
     // than they save (1242x375, D = 256: 281 us with them, 254 without)
     const long px = (long)width * height;
     if (ndisp > 128 && ndisp % 16 == 0 && npaths == 8) {
-        // uint16 slices of the largest frames: eight disparities per lane, one
-        // 16-byte store each, streamed to memory without half-written pieces
-        // (1920x1080, D = 256: 1689 us, 1921 with sixteen; 1280x720 818 and 787)
-        if (!slices_u8(p2) && px >= 1500000) return 2;
+        // uint16 slices of large volumes and the widest ranges: eight disparities
+        // per lane, one 16-byte store each, streamed to memory without
+        // half-written pieces.  Whole frames against the better of the other two,
+        // P2 = 880, a dozen sizes from 1200x1200 up: D = 256 2 .. 11% less, 240
+        // 0 .. 9% less, 224 4% less .. 4% more, 208 1% less .. 6% more, 192 3 .. 14%
+        // more; D = 256 below 300 M elements, thirty sizes: 4% less .. 8% more
+        if (!slices_u8(p2) && ndisp > 208 && px * ndisp >= 300000000L) return 2;
         if (width > 2 * height && px >= 400000) return 1;
     }
     const Frames size = {width, height, 1};

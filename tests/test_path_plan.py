@@ -82,3 +82,19 @@ def test_every_variant_with_the_largest_penalties(nd):
             np.testing.assert_array_equal(plan.disp[i].cpu().numpy(), o["disp"], err_msg=f"{shapes[i]} variant {v}")
             np.testing.assert_array_equal(plan.disp_right[i].cpu().numpy(), o["disp_right"])
         plan.close()
+
+
+def default_variant(lib, w, h, nd, npaths, p2):
+    f = getattr(lib, "_ZN3sgm15default_variantEiiiii")
+    f.restype = ctypes.c_int32
+    return f(w, h, nd, npaths, p2)
+
+
+# (width, height, D, the variant whose frame took least with P2 = 880, 8 paths)
+SLICES16 = [(1920, 1080, 144, 1), (1920, 1080, 160, 1), (1920, 1080, 192, 1), (1440, 1080, 160, 1), (2048, 800, 192, 1),
+            (1720, 960, 240, 2), (1600, 900, 256, 2), (1440, 1080, 256, 2), (1920, 1080, 256, 2), (2560, 720, 256, 2)]
+
+
+@pytest.mark.parametrize("w,h,nd,best", SLICES16)
+def test_layout_of_large_frames_with_two_byte_slices(lib, w, h, nd, best):
+    assert default_variant(lib, w, h, nd, 8, 880) == best

@@ -173,8 +173,25 @@ struct Frames {
     int width, height, count;
 };
 
-// The variant that run_time puts first; `runs` has room for npaths / 2 of them
-// per size.
+// Microseconds of the horizontal lines of a frame, which are one chain each.
+float chain_time(int width, const PathLayout& l) { return 1e-3f * (float)(width * l.ns_h); }
+
+// How long the pass over these frames takes in a layout; `runs` has room for
+// npaths / 2 of them per size.
+float pass_time(const Frames* sizes, int n, int npaths, const PathLayout& l, Run* runs) {
+    int m = 0;
+    for (int i = 0; i < n; ++i) {
+        const int w = sizes[i].width, h = sizes[i].height;
+        for (int q = 0; q < npaths / 2; ++q)
+            runs[m++] = {sizes[i].count * pair_blocks(q, w, h, l),
+                         q == 0 ? chain_time(w, l) : 1e-3f * (float)(h * (q == 1 ? l.ns_v : l.ns_d))};
+    }
+    // work lists start with the longest lines
+    if (n > 1 || sizes[0].count > 1) std::sort(runs, runs + m, [](const Run& a, const Run& b) { return a.us > b.us; });
+    return run_time(runs, m);
+}
+
+// The variant that pass_time puts first.
 int fastest_variant(const Frames* sizes, int n, int ndisp, int npaths, Run* runs) {
     const LayoutClass& c = layout_class(ndisp);
     if (c.n == 1) return 0;
@@ -182,20 +199,13 @@ int fastest_variant(const Frames* sizes, int n, int ndisp, int npaths, Run* runs
     float best_us = 0.0f;
     for (int v = 0; v < c.n; ++v) {
         if (!layout_takes(c.id[v], ndisp)) continue;
-        const PathLayout& l = kPathLayouts[c.id[v]];
-        int m = 0;
-        for (int i = 0; i < n; ++i) {
-            const int w = sizes[i].width, h = sizes[i].height;
-            for (int q = 0; q < npaths / 2; ++q)
-                runs[m++] = {sizes[i].count * pair_blocks(q, w, h, l),
-                             1e-3f * (q == 0 ? w * l.ns_h : h * (q == 1 ? l.ns_v : l.ns_d))};
-        }
-        // work lists start with the longest lines
-        if (n > 1 || sizes[0].count > 1) std::sort(runs, runs + m, [](const Run& a, const Run& b) { return a.us > b.us; });
-        const float us = run_time(runs, m);
+        const float us = pass_time(sizes, n, npaths, kPathLayouts[c.id[v]], runs);
         // up to D = 128 the first variant stays unless another is clearly
         // ahead: in wide frames it does better than reckoned (1242x375,
-        // D = 128, 4 paths: 107, the next 117)
+        // D = 128, 4 paths: 107, the next 117).  Mean loss against the best
+        // layout over 15 sizes, byte and 16-bit slices: D = 65 .. 128 0.5 and
+        // 1.0%, without this 1.2 and 2.1; 33 .. 64 0.1 and 0.4, without 0.3 and
+        // 1.0; 9 .. 32 the same with and without
         if (best < 0 || us < best_us * (best == 0 && ndisp <= 128 ? 0.92f : 1.0f)) {
             best = v;
             best_us = us;
@@ -232,10 +242,10 @@ int default_variant(const FrameSize* sizes, int n, int ndisp, int npaths) {
 }
 
 int default_variant(int width, int height, int ndisp, int npaths, int p2) {
-    // 8 paths of the widest ranges are bound by memory.  In wide frames helpers
-    // cost more there, reading the cost bytes of the horizontal lines once more,
-    // than they save (1242x375, D = 256: 281 us with them, 254 without)
     const long px = (long)width * height;
+    const Frames size = {width, height, 1};
+    Run runs[4];
+    // 8 paths of the widest ranges are bound by memory
     if (ndisp > 128 && ndisp % 16 == 0 && npaths == 8) {
         // uint16 slices of large volumes and the widest ranges: eight disparities
         // per lane, one 16-byte store each, streamed to memory without
@@ -244,10 +254,18 @@ int default_variant(int width, int height, int ndisp, int npaths, int p2) {
         // 0 .. 9% less, 224 4% less .. 4% more, 208 1% less .. 6% more, 192 3 .. 14%
         // more; D = 256 below 300 M elements, thirty sizes: 4% less .. 8% more
         if (!slices_u8(p2) && ndisp > 208 && px * ndisp >= 300000000L) return 2;
-        if (width > 2 * height && px >= 400000) return 1;
+        // In wide frames helpers, which read the cost bytes of the horizontal lines
+        // once more, cost more than reckoned; without them the pass is as long as
+        // the longer chain of such a line at least.  Whole frames, layout 1 against
+        // 0, chain of 1 by reckoned pass of 0: 1242x375 0.84, 3 .. 9% less (P2 =
+        // 880: 6% less .. 4% more); 1392x400 0.86, 9 .. 16% less (6% less .. 2%
+        // more); 2048x400 0.86, even; 3000x300 0.96, 5 .. 11% more; 1600x300 0.98,
+        // 5% less .. 9% more; 2048x200 1.04, 27% more; 4000x130 1.12, 36% more
+        if (width > 2 * height && px >= 400000) {
+            const PathLayout helped = path_layout(ndisp, 0), plain = path_layout(ndisp, 1);
+            if (chain_time(width, plain) < 0.9f * pass_time(&size, 1, npaths, helped, runs)) return 1;
+        }
     }
-    const Frames size = {width, height, 1};
-    Run runs[4];
     return fastest_variant(&size, 1, ndisp, npaths, runs);
 }
 

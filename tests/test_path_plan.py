@@ -98,3 +98,15 @@ SLICES16 = [(1920, 1080, 144, 1), (1920, 1080, 160, 1), (1920, 1080, 192, 1), (1
 @pytest.mark.parametrize("w,h,nd,best", SLICES16)
 def test_layout_of_large_frames_with_two_byte_slices(lib, w, h, nd, best):
     assert default_variant(lib, w, h, nd, 8, 880) == best
+
+
+# (width, height, the variant whose frame took least at D = 160 and 256, 8 paths)
+WIDE = [(1242, 375, 1), (1280, 400, 1), (1392, 400, 1), (2560, 1080, 1), (2048, 800, 1),
+        (2048, 200, 0), (1600, 260, 0), (3000, 300, 0), (4000, 130, 0), (32768, 16, 0)]
+
+
+@pytest.mark.parametrize("nd", [160, 256])
+@pytest.mark.parametrize("w,h,best", WIDE)
+def test_layout_of_wide_frames(lib, w, h, best, nd):
+    """Without helpers only where the chain of a horizontal line leaves room."""
+    assert default_variant(lib, w, h, nd, 8, 120) == best

@@ -186,7 +186,11 @@ float pass_time(const Frames* sizes, int n, int npaths, const PathLayout& l, Run
             runs[m++] = {sizes[i].count * pair_blocks(q, w, h, l),
                          q == 0 ? chain_time(w, l) : 1e-3f * (float)(h * (q == 1 ? l.ns_v : l.ns_d))};
     }
-    // work lists start with the longest lines
+    // The blocks that take longest first.  A work list starts with the blocks of
+    // most steps, which is not quite the same (a diagonal step takes up to three
+    // times a horizontal one): over 480 batches of small frames, reckoning in that
+    // order chooses as well (-23 .. +18%, 0.1% less in the geometric mean), and
+    // lists in this order run slower (0.4%; 64 pairs of 320x240, P2 = 880, 5 .. 8%)
     if (n > 1 || sizes[0].count > 1) std::sort(runs, runs + m, [](const Run& a, const Run& b) { return a.us > b.us; });
     return run_time(runs, m);
 }

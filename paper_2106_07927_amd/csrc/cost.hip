@@ -11,9 +11,11 @@
 // volume is written fully coalesced.  Bound by that write in large frames:
 // 1920x1080, D = 256: 531 MB in 120 us.  A D that is no multiple of 4 goes the
 // same way with dwords at any byte (1242x375, D = 101: 18 us, a byte per thread
-// took 47).
+// took 47).  In an image narrower than a run, shorter ones: 16x4000, D = 250 with
+// 32 pixels a thread 22 us, with 4 pixels 11 (a byte per thread 16).
 #include "sgm_internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace sgm {
@@ -169,19 +171,21 @@ __global__ __launch_bounds__(256) void cost_batch_vec4(WorkList wl) {
     }
 }
 
-// pixels per thread group and threads per block
-void vec4_shape(int ndisp, int* ppg, int* threads) {
+// pixels per thread group and threads per block, for runs of `pix` pixels
+// (staging a row needs 128 threads)
+void vec4_shape(int ndisp, int pix, int* ppg, int* threads) {
     const int dwords = (ndisp + 3) / 4;
-    const int need = (kCostPix * dwords + 255) / 256;          // pixels per group, at least
-    *ppg = need <= 1 ? 1 : need <= 2 ? 2 : need <= 4 ? 4 : need <= 8 ? 8 : need <= 16 ? 16 : 32;
-    *threads = dwords * ((kCostPix + *ppg - 1) / *ppg);
+    *ppg = 1;
+    while (dwords * ((pix + *ppg - 1) / *ppg) > 256) *ppg *= 2;        // 32 at most
+    *threads = std::max(128, dwords * ((pix + *ppg - 1) / *ppg));
 }
 
-// launch(PPG, RAGGED) with the run length of D as constants
+// launch(PPG, RAGGED) with the run length of D as constants; `pix` is kCostPix, or
+// the width of a narrower image
 template <typename Launch>
-void with_shape(int ndisp, const Launch& launch) {
+void with_shape(int ndisp, int pix, const Launch& launch) {
     int ppg, threads;
-    vec4_shape(ndisp, &ppg, &threads);
+    vec4_shape(ndisp, pix, &ppg, &threads);
     auto go = [&](auto p) {
         if (ndisp & 3) launch(p, std::true_type{}, threads);
         else launch(p, std::false_type{}, threads);
@@ -198,7 +202,7 @@ void with_shape(int ndisp, const Launch& launch) {
 
 hipError_t launch_cost(const Frame& f, hipStream_t stream) {
     const dim3 grid(cost_blocks_x(f.width), f.height);
-    with_shape(f.ndisp, [&](auto ppg, auto ragged, int threads) {
+    with_shape(f.ndisp, std::min(kCostPix, f.width), [&](auto ppg, auto ragged, int threads) {
         cost_kernel_vec4<ppg.value, ragged.value>
             <<<grid, threads, 0, stream>>>(f.census_left, f.census_right, f.width, f.ndisp, f.cost);
     });
@@ -207,7 +211,7 @@ hipError_t launch_cost(const Frame& f, hipStream_t stream) {
 
 hipError_t launch_cost_batch(const WorkList& wl, int ndisp, hipStream_t stream) {
     const int grid = persistent_grid(wl.total);
-    with_shape(ndisp, [&](auto ppg, auto ragged, int threads) {
+    with_shape(ndisp, kCostPix, [&](auto ppg, auto ragged, int threads) {
         cost_batch_vec4<ppg.value, ragged.value><<<grid, threads, 0, stream>>>(wl);
     });
     return hipGetLastError();

@@ -46,10 +46,9 @@ size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 // Workspace of sgm_aggregate_select: path slices, room for S_bar (D no multiple
 // of 16; not used), D^R keys, D^L.  Returns the total bytes.
 size_t select_layout(int32_t width, int32_t height, int32_t ndisp, int32_t npaths, int32_t p2,
-                     size_t* agg_off, size_t* keys_off, size_t* dl_off) {
+                     size_t* keys_off, size_t* dl_off) {
     const size_t n = (size_t)width * height;
     size_t off = align256(sgm::aggregate_work_bytes(width, height, ndisp, npaths, p2));
-    *agg_off = off;
     if (sgm::workspace_holds_agg(ndisp)) off += align256(2 * n * (size_t)ndisp);
     *keys_off = off;
     off += align256(4 * n);
@@ -67,8 +66,7 @@ bool good_params(const sgm_params* p) {
 
 // Workspace of the exact-check path, byte offsets.
 struct ExactLayout {
-    size_t ref, mat, census_left, census_right, cost, select, agg, keys, dl, disp_left,
-        disp_flipped;
+    size_t ref, mat, census_left, census_right, cost, slices, disp_left, disp_flipped;
 };
 
 size_t exact_layout(int32_t width, int32_t height, int32_t ndisp, const sgm_params* p,
@@ -85,8 +83,9 @@ size_t exact_layout(int32_t width, int32_t height, int32_t ndisp, const sgm_para
     off += align256(8 * n);
     l->cost = off;
     off += align256(n * (size_t)ndisp);
-    l->select = off;
-    off += select_layout(width, height, ndisp, p->npaths, p->p2, &l->agg, &l->keys, &l->dl);
+    l->slices = off;                // the size of sgm_aggregate_select's workspace, of which
+    size_t keys, dl;                // the passes use the slices
+    off += select_layout(width, height, ndisp, p->npaths, p->p2, &keys, &dl);
     l->disp_left = off;
     off += align256(2 * n);
     l->disp_flipped = off;
@@ -252,8 +251,8 @@ size_t sgm_aggregate_select_work_bytes(int32_t width, int32_t height, int32_t nd
                                        int32_t npaths, int32_t p2) {
     if (bad_size(width, height) || bad_volume(width, height, ndisp) || bad_penalties(npaths, 0, p2))
         return 0;
-    size_t a, k, d;
-    return select_layout(width, height, ndisp, npaths, p2, &a, &k, &d);
+    size_t k, d;
+    return select_layout(width, height, ndisp, npaths, p2, &k, &d);
 }
 
 int32_t sgm_aggregate_select(const uint8_t* cost, int32_t width, int32_t height, int32_t ndisp,
@@ -263,8 +262,8 @@ int32_t sgm_aggregate_select(const uint8_t* cost, int32_t width, int32_t height,
     if (!cost || !disp_out || bad_size(width, height)) return SGM_ERR_ARG;
     if (bad_volume(width, height, ndisp) || bad_penalties(npaths, p1, p2)) return SGM_ERR_ARG;
     if (median3x3 != 0 && median3x3 != 1) return SGM_ERR_ARG;
-    size_t agg_off, keys_off, dl_off;
-    const size_t need = select_layout(width, height, ndisp, npaths, p2, &agg_off, &keys_off, &dl_off);
+    size_t keys_off, dl_off;
+    const size_t need = select_layout(width, height, ndisp, npaths, p2, &keys_off, &dl_off);
     if (!work || work_bytes < need) return SGM_ERR_WORKSPACE;
     if (!aligned(cost, 16) || !aligned(work, 256) || !aligned(disp_out, 4) ||
         (disp_right_out && !aligned(disp_right_out, 4)))
@@ -304,8 +303,8 @@ int32_t sgm_aggregate_select_subpixel(const uint8_t* cost, int32_t width, int32_
     if (!cost || !disp_out || bad_size(width, height)) return SGM_ERR_ARG;
     if (bad_volume(width, height, ndisp) || bad_penalties(npaths, p1, p2)) return SGM_ERR_ARG;
     if (median3x3 != 0 && median3x3 != 1) return SGM_ERR_ARG;
-    size_t agg_off, keys_off, dl_off;
-    const size_t fine_off = select_layout(width, height, ndisp, npaths, p2, &agg_off, &keys_off, &dl_off);
+    size_t keys_off, dl_off;
+    const size_t fine_off = select_layout(width, height, ndisp, npaths, p2, &keys_off, &dl_off);
     const size_t need = fine_off + align256(4 * (size_t)width * height);
     if (!work || work_bytes < need) return SGM_ERR_WORKSPACE;
     if (!aligned(cost, 16) || !aligned(work, 256) || !aligned(disp_out, 4) ||
@@ -371,7 +370,7 @@ int32_t sgm_disparity_exact_lr(const uint8_t* left, const uint8_t* right, int32_
     f.census_left = reinterpret_cast<uint64_t*>(base + l.census_left);
     f.census_right = reinterpret_cast<uint64_t*>(base + l.census_right);
     f.cost = reinterpret_cast<uint8_t*>(base + l.cost);
-    f.slices = reinterpret_cast<uint8_t*>(base + l.select);
+    f.slices = reinterpret_cast<uint8_t*>(base + l.slices);
     f.slice_stride = sgm::aggregate_slice_elems(width, height, ndisp);
     uint16_t* dl = reinterpret_cast<uint16_t*>(base + l.disp_left);
     uint16_t* flipped = reinterpret_cast<uint16_t*>(base + l.disp_flipped);

@@ -20,16 +20,8 @@ __device__ __forceinline__ u16x2 as_u16x2(uint32_t v) { return __builtin_bit_cas
 __device__ __forceinline__ uint32_t as_u32(u16x2 v) { return __builtin_bit_cast(uint32_t, v); }
 
 __device__ __forceinline__ uint32_t pk_add(uint32_t a, uint32_t b) { return as_u32(as_u16x2(a) + as_u16x2(b)); }
-__device__ __forceinline__ uint32_t pk_sub(uint32_t a, uint32_t b) { return as_u32(as_u16x2(a) - as_u16x2(b)); }
 __device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {
     return as_u32(__builtin_elementwise_min(as_u16x2(a), as_u16x2(b)));
-}
-__device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
-    return as_u32(__builtin_elementwise_max(as_u16x2(a), as_u16x2(b)));
-}
-// (lo, hi) of the result = (hi of b, lo of a): the pair one element down.
-__device__ __forceinline__ uint32_t pk_shift_in(uint32_t a, uint32_t b) {
-    return __builtin_amdgcn_alignbit(a, b, 16);
 }
 __host__ __device__ __forceinline__ uint32_t pk_splat(uint32_t v16) { return v16 | (v16 << 16); }
 
@@ -112,7 +104,6 @@ enum : int {
     kDppQuadSwap2 = 0x4E,   // quad_perm [2,3,0,1]
     kDppRowShl1 = 0x101,
     kDppRowShr1 = 0x111,
-    kDppRowRor1 = 0x121,
     kDppRowMirror = 0x140,
     kDppRowHalfMirror = 0x141,
 };
@@ -120,41 +111,6 @@ enum : int {
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp(uint32_t old, uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, 0xF, 0xF, false);
-}
-
-// Minimum over the GROUP consecutive lanes of an aligned group (GROUP a power
-// of two, at most 16), returned to every lane of the group.
-template <int GROUP>
-__device__ __forceinline__ uint32_t group_min(uint32_t v) {
-    if constexpr (GROUP >= 2) v = min(v, dpp<kDppQuadSwap1>(0u, v));
-    if constexpr (GROUP >= 4) v = min(v, dpp<kDppQuadSwap2>(0u, v));
-    if constexpr (GROUP >= 8) v = min(v, dpp<kDppRowHalfMirror>(0u, v));
-    if constexpr (GROUP >= 16) v = min(v, dpp<kDppRowMirror>(0u, v));
-    return v;
-}
-
-// Value of the next lane of the group; the group's last lane gets `edge`.
-template <int GROUP>
-__device__ __forceinline__ uint32_t group_next(uint32_t v, uint32_t edge, bool last) {
-    if constexpr (GROUP == 1) {
-        return edge;
-    } else {
-        uint32_t r = dpp<kDppRowShl1>(edge, v);
-        if constexpr (GROUP < 16) r = last ? edge : r;
-        return r;
-    }
-}
-
-// Value of the previous lane of the group; the group's first lane gets `edge`.
-template <int GROUP>
-__device__ __forceinline__ uint32_t group_prev(uint32_t v, uint32_t edge, bool first) {
-    if constexpr (GROUP == 1) {
-        return edge;
-    } else {
-        uint32_t r = dpp<kDppRowShr1>(edge, v);
-        if constexpr (GROUP < 16) r = first ? edge : r;
-        return r;
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -228,7 +184,6 @@ __host__ __device__ inline int cost_blocks_x(int w) { return (w + kCostPix - 1) 
 // (at most 8192 volume elements per tile, so every thread sums two 16-byte
 // blocks: 64 pixels up to D = 128, 32 beyond)
 constexpr int kFusedTile = 64;
-constexpr int kMaxFusedD = 256;
 __host__ __device__ inline int fused_tile_px(int ndisp) { return ndisp > 128 ? 32 : kFusedTile; }
 __host__ __device__ inline int fused_blocks_x(int w, int ndisp) {
     const int t = fused_tile_px(ndisp);
@@ -343,8 +298,9 @@ int path_blocks(int width, int height, int ndisp, int npaths, int variant);
 int path_horizontal_blocks(int width, int height, int ndisp, int variant);
 size_t aggregate_slice_elems(int width, int height, int ndisp);
 size_t aggregate_work_bytes(int width, int height, int ndisp, int npaths, int p2);
-// Workspaces of the streamlined forms keep room for S_bar at such a D (their
-// sizes are part of the interface); nothing is stored there.
+// The streamlined forms' workspaces have room for S_bar at such a D, in which
+// nothing is stored: the sizes that the *_work_bytes queries give are fixed (a
+// test of the interface holds them).
 inline bool workspace_holds_agg(int ndisp) { return ndisp % 16 != 0; }
 
 // ---------------------------------------------------------------------------

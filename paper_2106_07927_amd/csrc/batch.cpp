@@ -4,8 +4,8 @@
 // Plan creation lays every frame's intermediates out in the caller's
 // workspace, groups the frames by what the kernels are compiled for
 // (disparity range, and for the path pass the lane-layout variant chosen by
-// the tuning table or for all blocks of the range), writes one device work list per stage and group, and
-// captures the whole sequence into a hipGraph:
+// the tuning table or for all blocks of the range), writes one device work
+// list per stage and group, and captures the whole sequence into a hipGraph:
 //     census (all frames, both images) -> cost (per D) -> paths (per D and
 //     variant) -> D^R key fill (all) -> path sum fused with the selection
 //     (per D) -> LR check + median (all)
@@ -226,7 +226,9 @@ size_t build_layout(const sgm_pair* pairs, int32_t n, const sgm_params* p, const
         if (L.stage == kPaths) {
             size_t items = 0;
             for (int k : L.frames) {
-                // room for any variant's blocks: the size does not depend on the table
+                // room for any variant's blocks, so that no table needs less than
+                // none does (one with several variants makes more launches, and
+                // their tables take more)
                 const Frame& f = (*frames)[k];
                 int most = 0;
                 for (int v = 0; v < path_variants(f.ndisp); ++v)

@@ -35,7 +35,7 @@
 // all but small frames (per volume element 8 + 4 + 1 bytes for 8 paths, where
 // storing the first half's values instead took 8 + 8 + 4); the steps walked
 // twice cost less than the bytes they save: 1920x1080, D = 256: 1910 -> 1102
-// us (6.2 TB/s), 1242x375, D = 128: 182 -> 134 us, with P2 = 880: 320 -> 203 us.
+// us (6.2 TB/s), 1242x375, D = 128: 182 -> 134 us, with P2 = 880: 320 -> 192 us.
 // In small frames a line is a chain that nothing else hides.  There two more
 // waves per line group (PathLayout::help_*) walk the partner's steps and hand
 // them over through LDS, a chunk ahead: 320x240, D = 64, 4 paths: 30 -> 24 us
@@ -63,10 +63,11 @@
 // grows to 16 * 255 at most, a real state to m + P2 + 255, padding to twice P2
 // (below), and with P1 <= P2 added that is 0x7C00 only where P2 > 7936
 // (kNarrowP2); a larger one, which 4 paths may have, takes two minima
-// (1242x375, D = 128, P2 = 880: 212 us with two, 203 with one).  m is a tree over
-// the registers and an all-reduce over the line's lanes that runs beside the
-// neighbour terms.  Disparities beyond D (padding) are lifted by 255 + P2 in
-// every step: as neighbours they never come below m + P2, and m never is one.
+// (1242x375, D = 128, 4 paths: 126 us with two at P2 = 7937, 116 with one at
+// 7936).  m is a tree over the registers and an all-reduce over the line's lanes
+// that runs beside the neighbour terms.  Disparities beyond D (padding) are
+// lifted by 255 + P2 in every step: as neighbours they never come below m + P2,
+// and m never is one.
 //
 // Where D cuts a lane's disparities (RAGGED) the accesses stay whole vectors,
 // at any byte alignment; only the lane that holds d = D - 1 stores its values

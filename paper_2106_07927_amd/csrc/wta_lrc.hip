@@ -49,12 +49,13 @@ __device__ __forceinline__ float refine(int d, uint32_t s_prev, uint32_t s_min, 
 //      segment's minimum for q = x - D + 1.  The segments meet in LDS, then
 //      one atomicMin per q merges the tile into the D^R key map.  Up to 32
 //      disparities a wave walks two or four segments at once, GL lanes each
-//      (selection from S_bar, 640x480, D = 16: 10.9 us with one, now 6.8).
+//      (selection from S_bar, 640x480, D = 16: 8.4 us with a thread per q,
+//      10.9 with one segment a wave, now 6.8).
 // Keys are built with one byte permute per value (the disparity bytes of a
 // lane are constants).  The fused form is bound by the bytes it reads (NS + 1
 // per element: 46 us at 1242x375, D = 128, 6.5 TB/s); the pass over S_bar was
 // bound by its instructions (17 per element, D^R folded by one thread per q:
-// 33 us) before (2) and (3) took this form, 25 us since.
+// 33 us) before (2) and (3) took this form, 24 us since.
 // NS pair slices: uint8 (S_bar = 2 NS C + sum) or uint16 (S_bar = sum).
 struct TileShape {
     int rs, tpx, width, ndisp, x0, npx;

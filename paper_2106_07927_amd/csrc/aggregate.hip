@@ -138,13 +138,33 @@ struct Run {
 // blocks that share one cost the longest's time plus half of the others'.
 // Against timed passes of 16 .. 256 disparities, 4 and 8 paths, 160x120 ..
 // 1920x1080: off by 5% in the mean while memory does not bound the pass.
-// A batch plan may reckon thousands of runs, so each is dealt once: its whole
-// rounds over the units as one sum, the rest block by block (4,000 pairs of one
-// size: 1 ms, all of different sizes: 10 ms; holding every run against every
-// other took 660 ms and more).
-float run_time(const Run* runs, int n) {
-    constexpr int kUnits = 256;
-    constexpr float kShared = 0.5f;
+constexpr int kUnits = 256;
+float shared_time(float sum, float longest) { return longest + 0.5f * (sum - longest); }
+
+// Of a few runs (a frame's, on every call): what a unit holds changes only where
+// a run begins, so each of these is reckoned.
+float run_time_few(const Run* runs, int n) {
+    float worst = 0.0f;
+    for (int k = 0, first = 0; k < n; first += runs[k++].blocks) {
+        float sum = 0.0f, longest = 0.0f;
+        int b = first % kUnits;                        // the unit's next block
+        for (int at = 0, end = 0; at < n; ++at) {
+            end += runs[at].blocks;
+            for (; b < end; b += kUnits) {
+                sum += runs[at].us;
+                longest = std::max(longest, runs[at].us);
+            }
+        }
+        worst = std::max(worst, shared_time(sum, longest));
+    }
+    return worst;
+}
+
+// Of many (a batch plan may have thousands): each is dealt once, its whole rounds
+// over the units as one sum, the rest block by block (4,000 pairs of one size:
+// 1 ms, all of different sizes: 10 ms; reckoned as above 660 ms and more).  Not
+// for a few: the 256 units cost a call 1 us.
+float run_time_many(const Run* runs, int n) {
     float sum[kUnits] = {}, longest[kUnits] = {};
     float every_sum = 0.0f, every_longest = 0.0f;      // of the whole rounds, on every unit
     int unit = 0;
@@ -161,12 +181,12 @@ float run_time(const Run* runs, int n) {
         }
     }
     float worst = 0.0f;
-    for (int u = 0; u < kUnits; ++u) {
-        const float most = std::max(longest[u], every_longest);
-        worst = std::max(worst, most + kShared * (sum[u] + every_sum - most));
-    }
+    for (int u = 0; u < kUnits; ++u)
+        worst = std::max(worst, shared_time(sum[u] + every_sum, std::max(longest[u], every_longest)));
     return worst;
 }
+
+float run_time(const Run* runs, int n) { return n <= 4 ? run_time_few(runs, n) : run_time_many(runs, n); }
 
 // `count` frames of one size.
 struct Frames {

@@ -77,7 +77,7 @@ def parse():
 # 2.4 GHz and the kernels' durations).  An entry holds only for the kernel
 # sources whose digest it names; otherwise the figures are null.
 COUNTERS = {
-    "sgm_aggregate_select": {"sources": "7162c4e62f0bb6ea", "traffic": 1048.8, "valu_busy": 0.611},
+    "sgm_aggregate_select": {"sources": "b5005c70c7307ff1", "traffic": 1048.8, "valu_busy": 0.613},
 }
 
 KERNEL_SOURCES = ("census.hip", "cost.hip", "aggregate.hip", "paths.hip", "wta_lrc.hip",
